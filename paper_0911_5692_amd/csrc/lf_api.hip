@@ -140,7 +140,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
     size_t state[2][4];
-    size_t part, mom, enp, enout, tot, P, S, C;
+    size_t part[2], mom, enp, enout, tot, P, S[2], C;
     size_t total;
 };
 
@@ -156,13 +156,20 @@ Layout layout_of(const lf_params *p)
             L.state[b][j] = off;
             off = align_up(off + n3 * esize(p->dtype));
         }
-    L.part = off; off = align_up(off + (size_t)shape_of(p).rows * kNPart * sizeof(double));
+    const size_t rows = (size_t)shape_of(p).rows;
+    for (int b = 0; b < 2; ++b) {
+        L.part[b] = off;
+        off = align_up(off + rows * kNPart * sizeof(double));
+    }
     L.mom = off; off = align_up(off + (size_t)kRedBlocks * kNMom * sizeof(double));
     L.enp = off; off = align_up(off + (size_t)kRedBlocks * kNEn * sizeof(double));
     L.enout = off; off = align_up(off + 16 * sizeof(double));
     L.tot = off; off = align_up(off + 8 * sizeof(double));
     L.P = off; off = align_up(off + sizeof(DevParams));
-    L.S = off; off = align_up(off + sizeof(DevScalars));
+    for (int b = 0; b < 2; ++b) {
+        L.S[b] = off;
+        off = align_up(off + sizeof(DevScalars));
+    }
     L.C = off; off = align_up(off + sizeof(CoefPair));
     L.total = off;
     return L;
@@ -209,10 +216,14 @@ struct lf_ctx {
     char *ws;
     void *buf[2][4];
     int cur;
-    double *part, *mom, *enp, *enout, *tot;
+    // by buffer parity, as buf: a step reads the sums and scalars that belong
+    // to its input arrays and writes those of its output arrays
+    double *part[2];
+    DevScalars *S[2];
+    double *mom, *enp, *enout, *tot;
     DevParams *P;
-    DevScalars *S;
     CoefPair *C;
+    int extra;          // StepSource::extra of its sweeps
     int inited;
     // g[j][p]: 2^j steps from buffer parity p, j = 0 .. logK (K = 2^logK
     // steps per long graph).  An n-step call launches n div K long graphs and
@@ -233,23 +244,30 @@ struct lf_ctx {
 
 namespace {
 
-// One leapfrog step: FP64 scale-factor update from the pending partial sums,
-// then the fused kick-drift sweep from the arrays `in` into `out`, which
-// leaves the partial sums of the new fields for the next step.
-void enqueue_step_io(lf_ctx *c, const void *const in[4], void *const out[4], hipStream_t st, hipEvent_t *ev,
+// Whether the sweep forms the scale-factor update in its own blocks.
+bool step_fused(const lf_ctx *c) { return c->sh.tile_y != 1 && c->sh.rows <= kFusedRows; }
+
+// One leapfrog step: FP64 scale-factor update from the pending partial sums
+// and scalars of parity p, and the fused kick-drift sweep from the arrays
+// `in` into `out`, which leaves the partial sums of the new fields for the
+// next step; sums and scalars of the new state go to parity p ^ 1.
+void enqueue_step_io(lf_ctx *c, int p, const void *const in[4], void *const out[4], hipStream_t st, hipEvent_t *ev,
                      DevScalars *tape = nullptr)
 {
+    const StepSource fused{c->part[p], c->sh.rows, c->P, c->S[p], c->S[p ^ 1], c->C, tape, c->extra};
+    StepSource given{};
+    given.C = c->C;
     if (ev) (void)hipEventRecord(ev[0], st);
-    launch_aupdate(c->part, c->sh.rows, c->P, c->S, c->C, st, tape);
+    if (!step_fused(c)) launch_aupdate(c->part[p], c->sh.rows, c->P, c->S[p], c->S[p ^ 1], c->C, st, tape);
     if (ev) (void)hipEventRecord(ev[1], st);
     if (c->sh.tile_y == 1) {
         launch_sweep_plain(stencil_of(&c->p), c->p.dtype, c->p.beta, in, out, c->p.N, c->C, st);
         if (ev) (void)hipEventRecord(ev[2], st);
-        launch_reduce(stencil_of(&c->p), c->p.dtype, out[0], out[1], c->p.N, c->S->bg_f, c->p.beta, c->part,
-                      c->sh.rows, st);
+        launch_reduce(stencil_of(&c->p), c->p.dtype, out[0], out[1], c->p.N, c->S[p ^ 1]->bg_f, c->p.beta,
+                      c->part[p ^ 1], c->sh.rows, st);
     } else {
         launch_sweep_lds(stencil_of(&c->p), c->p.dtype, c->sh.tile_x, c->sh.tile_y, c->p.beta, in, out, c->p.N,
-                         c->sh.zchunk, c->C, c->part, st);
+                         c->sh.zchunk, step_fused(c) ? fused : given, c->part[p ^ 1], st);
         if (ev) (void)hipEventRecord(ev[2], st);
     }
     if (ev) (void)hipEventRecord(ev[3], st);
@@ -260,7 +278,7 @@ void enqueue_step(lf_ctx *c, int cur, hipStream_t st, hipEvent_t *ev)
 {
     const void *in[4] = {c->buf[cur][0], c->buf[cur][1], c->buf[cur][2], c->buf[cur][3]};
     void *out[4] = {c->buf[cur ^ 1][0], c->buf[cur ^ 1][1], c->buf[cur ^ 1][2], c->buf[cur ^ 1][3]};
-    enqueue_step_io(c, in, out, st, ev);
+    enqueue_step_io(c, cur, in, out, st, ev);
 }
 
 // Makes dev the current device for the scope and restores the caller's on
@@ -440,15 +458,22 @@ int lf_create(const lf_params *p, void *stream, void *workspace, size_t ws_bytes
     c->ws = (char *)workspace;
     for (int b = 0; b < 2; ++b)
         for (int j = 0; j < 4; ++j) c->buf[b][j] = c->ws + L.state[b][j];
-    c->part = (double *)(c->ws + L.part);
+    for (int b = 0; b < 2; ++b) {
+        c->part[b] = (double *)(c->ws + L.part[b]);
+        c->S[b] = (DevScalars *)(c->ws + L.S[b]);
+    }
     c->mom = (double *)(c->ws + L.mom);
     c->enp = (double *)(c->ws + L.enp);
     c->enout = (double *)(c->ws + L.enout);
     c->tot = (double *)(c->ws + L.tot);
     c->P = (DevParams *)(c->ws + L.P);
-    c->S = (DevScalars *)(c->ws + L.S);
     c->C = (CoefPair *)(c->ws + L.C);
     c->logK = (p->N >= 256) ? 3 : 5;
+    // a grid that leaves room on the device takes one block more for what one
+    // block has to write (32^3 FP64: 8.0 us a step against 8.8 with that work
+    // at the end of a tile's block); in a full one it would wait for a tile's
+    // block to end
+    c->extra = c->sh.tile_y != 1 && c->sh.rows < resident_blocks(p, c->sh.tile_x, c->sh.tile_y) ? 1 : 0;
     hipError_t e;
     DevParams dp;
     fill_dev_params(p, &dp);
@@ -490,10 +515,10 @@ static int init_common(lf_ctx *c, const void *f1, const void *f2, const void *v1
     if (!isfinite(ad0)) return fail(LF_EINVAL, "ad0 must be finite");
     const int N = c->p.N;
     launch_input_moments(stencil_of(&c->p), in_dtype, f1, f2, v1, v2, N, c->p.beta, c->mom, kRedBlocks, c->stream);
-    launch_init_scalars(c->mom, kRedBlocks, c->P, c->S, physical, a0, ad0, c->stream);
+    launch_init_scalars(c->mom, kRedBlocks, c->P, c->S[0], physical, a0, ad0, c->stream);
     launch_init_fields(c->p.dtype, in_dtype, f1, f2, v1, v2, c->buf[0][0], c->buf[0][1],
-                       c->buf[0][2], c->buf[0][3], N, c->P, c->S, c->stream);
-    launch_reduce(stencil_of(&c->p), c->p.dtype, c->buf[0][0], c->buf[0][1], N, c->S->bg_f, c->p.beta, c->part,
+                       c->buf[0][2], c->buf[0][3], N, c->P, c->S[0], c->stream);
+    launch_reduce(stencil_of(&c->p), c->p.dtype, c->buf[0][0], c->buf[0][1], N, c->S[0]->bg_f, c->p.beta, c->part[0],
                   c->sh.rows, c->stream);
     HIPCHK(hipGetLastError());
     c->cur = 0;
@@ -517,7 +542,7 @@ int lf_init_physical(lf_ctx *c, const void *f1, const void *f2, const void *u1, 
     int rc = init_common(c, f1, f2, u1, u2, in_dtype, a0, 0.0, 1);
     if (rc) return rc;
     DevScalars hs;
-    HIPCHK(hipMemcpyAsync(&hs, c->S, sizeof hs, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipMemcpyAsync(&hs, c->S[0], sizeof hs, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     *ad0_out = hs.ad0;
     if (hs.status) return fail(LF_ENONFINITE, "non-finite initial state or Friedmann constraint");
@@ -572,7 +597,7 @@ int lf_energies(lf_ctx *c, lf_report *out)
     if (!c || !out) return fail(LF_EINVAL, "NULL argument");
     if (!c->inited) return fail(LF_ESTATE, "lf_energies before lf_init");
     const void *s4[4] = {c->buf[c->cur][0], c->buf[c->cur][1], c->buf[c->cur][2], c->buf[c->cur][3]};
-    launch_energy(stencil_of(&c->p), c->p.dtype, s4, c->p.N, c->P, c->S, c->enp, kRedBlocks, c->enout, c->stream);
+    launch_energy(stencil_of(&c->p), c->p.dtype, s4, c->p.N, c->P, c->S[c->cur], c->enp, kRedBlocks, c->enout, c->stream);
     HIPCHK(hipGetLastError());
     double h[12];
     HIPCHK(hipMemcpyAsync(h, c->enout, sizeof h, hipMemcpyDeviceToHost, c->stream));
@@ -604,7 +629,7 @@ int lf_rho_p(lf_ctx *c, void *rho, void *p, int out_dtype, double *avg)
         return fail(LF_EINVAL, "output arrays must be 256-byte aligned");
     const void *s4[4] = {c->buf[c->cur][0], c->buf[c->cur][1], c->buf[c->cur][2], c->buf[c->cur][3]};
     // the energy partial rows (kRedBlocks x kNEn doubles) hold the 2 sums here
-    launch_rho_p(stencil_of(&c->p), c->p.dtype, out_dtype, s4, rho, p, c->p.N, c->P, c->S, c->enp, kRedBlocks, c->enout, c->stream);
+    launch_rho_p(stencil_of(&c->p), c->p.dtype, out_dtype, s4, rho, p, c->p.N, c->P, c->S[c->cur], c->enp, kRedBlocks, c->enout, c->stream);
     HIPCHK(hipGetLastError());
     double h[3];
     HIPCHK(hipMemcpyAsync(h, c->enout, sizeof h, hipMemcpyDeviceToHost, c->stream));
@@ -622,7 +647,7 @@ int lf_get_fields(lf_ctx *c, void *f1, void *f2, void *v1, void *v2, int out_dty
     for (int j = 0; j < 4; ++j)
         if (o[j] && (uintptr_t)o[j] % kAlign) return fail(LF_EINVAL, "output %d not 256-byte aligned", j);
     const void *s4[4] = {c->buf[c->cur][0], c->buf[c->cur][1], c->buf[c->cur][2], c->buf[c->cur][3]};
-    launch_get_fields(c->p.dtype, out_dtype, s4, o, c->p.N, c->P, c->S, synchronized ? 1 : 0, c->stream);
+    launch_get_fields(c->p.dtype, out_dtype, s4, o, c->p.N, c->P, c->S[c->cur], synchronized ? 1 : 0, c->stream);
     HIPCHK(hipGetLastError());
     return LF_OK;
 }
@@ -638,11 +663,11 @@ int lf_get_state(lf_ctx *c, void *d1, void *d2, void *e1, void *e2, lf_scalars *
     const size_t bytes = (size_t)c->p.N * c->p.N * c->p.N * esize(c->p.dtype);
     for (int j = 0; j < 4; ++j)
         HIPCHK(hipMemcpyAsync(o[j], c->buf[c->cur][j], bytes, hipMemcpyDeviceToDevice, c->stream));
-    launch_sum_partials(c->part, c->sh.rows, kNPart, c->tot, c->stream);
+    launch_sum_partials(c->part[c->cur], c->sh.rows, kNPart, c->tot, c->stream);
     HIPCHK(hipGetLastError());
     DevScalars hs;
     double tot[kNPart];
-    HIPCHK(hipMemcpyAsync(&hs, c->S, sizeof hs, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipMemcpyAsync(&hs, c->S[c->cur], sizeof hs, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipMemcpyAsync(tot, c->tot, sizeof tot, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     memset(s, 0, sizeof *s);
@@ -683,9 +708,10 @@ int lf_set_state(lf_ctx *c, const void *d1, const void *d2, const void *e1, cons
     hs.status = s->status;
     double tot[8] = {0};
     for (int i = 0; i < kNPart; ++i) tot[i] = s->pend[i];
-    HIPCHK(hipMemcpyAsync(c->S, &hs, sizeof hs, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(hipMemcpyAsync(c->S[0], &hs, sizeof hs, hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(c->tot, tot, sizeof tot, hipMemcpyHostToDevice, c->stream));
-    launch_set_pending(c->part, c->sh.rows, c->tot, c->stream);
+    launch_set_powers(c->P, c->S[0], c->stream);
+    launch_set_pending(c->part[0], c->sh.rows, c->tot, c->stream);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(c->stream));
     c->cur = 0;
@@ -912,14 +938,14 @@ int save_slot(lf_ctx *c, char *slot, const AdjLayout &L)
     for (int j = 0; j < 4; ++j)
         HIPCHK(hipMemcpyAsync(slot + j * L.arr_bytes, c->buf[c->cur][j], bytes, hipMemcpyDeviceToDevice, c->stream));
     char *sc = slot + 4 * L.arr_bytes;
-    HIPCHK(hipMemcpyAsync(sc, c->S, sizeof(DevScalars), hipMemcpyDeviceToDevice, c->stream));
-    launch_sum_partials(c->part, c->sh.rows, kNPart, (double *)(sc + align_up(sizeof(DevScalars))), c->stream);
+    HIPCHK(hipMemcpyAsync(sc, c->S[c->cur], sizeof(DevScalars), hipMemcpyDeviceToDevice, c->stream));
+    launch_sum_partials(c->part[c->cur], c->sh.rows, kNPart, (double *)(sc + align_up(sizeof(DevScalars))), c->stream);
     HIPCHK(hipGetLastError());
     return LF_OK;
 }
 
 // Checkpoint `slot` back: its four arrays into `arrays` (4 x arr_bytes apart),
-// its scalars and pending sums into the context.
+// its scalars and pending sums into the context (parity 0).
 int restore_slot(lf_ctx *c, const char *slot, char *arrays, const AdjLayout &L, hipStream_t st)
 {
     const size_t bytes = (size_t)c->p.N * c->p.N * c->p.N * esize(c->p.dtype);
@@ -927,8 +953,8 @@ int restore_slot(lf_ctx *c, const char *slot, char *arrays, const AdjLayout &L, 
         HIPCHK(hipMemcpyAsync(arrays + j * L.arr_bytes, slot + j * L.arr_bytes, bytes, hipMemcpyDeviceToDevice,
                               st));
     const char *sc = slot + 4 * L.arr_bytes;
-    HIPCHK(hipMemcpyAsync(c->S, sc, sizeof(DevScalars), hipMemcpyDeviceToDevice, st));
-    launch_set_pending(c->part, c->sh.rows, (const double *)(sc + align_up(sizeof(DevScalars))), st);
+    HIPCHK(hipMemcpyAsync(c->S[0], sc, sizeof(DevScalars), hipMemcpyDeviceToDevice, st));
+    launch_set_pending(c->part[0], c->sh.rows, (const double *)(sc + align_up(sizeof(DevScalars))), st);
     HIPCHK(hipGetLastError());
     return LF_OK;
 }
@@ -952,9 +978,9 @@ int recompute_segment(lf_ctx *c, char *ws, const AdjLayout &L, int64_t s, int b,
             char *a = seg + (size_t)j * 4 * L.arr_bytes, *nb = a + 4 * L.arr_bytes;
             const void *in[4] = {a, a + L.arr_bytes, a + 2 * L.arr_bytes, a + 3 * L.arr_bytes};
             void *out[4] = {nb, nb + L.arr_bytes, nb + 2 * L.arr_bytes, nb + 3 * L.arr_bytes};
-            enqueue_step_io(c, in, out, st, nullptr, tape + j);
+            enqueue_step_io(c, (int)(j & 1), in, out, st, nullptr, tape + j);
         } else {
-            HIPCHK(hipMemcpyAsync(tape + j, c->S, sizeof(DevScalars), hipMemcpyDeviceToDevice, st));
+            HIPCHK(hipMemcpyAsync(tape + j, c->S[j & 1], sizeof(DevScalars), hipMemcpyDeviceToDevice, st));
         }
     }
     HIPCHK(hipGetLastError());
@@ -1029,7 +1055,7 @@ int lf_adj_backward(lf_ctx *c, double dL, double *dL_dG, void *g_f1, void *g_f2,
     HIPCHK(hipMemcpyAsync(wd, hw, sizeof hw, hipMemcpyHostToDevice, c->stream));
     // seed: cotangent of the final state
     const void *s4[4] = {c->buf[c->cur][0], c->buf[c->cur][1], c->buf[c->cur][2], c->buf[c->cur][3]};
-    launch_adj_seed(stencil_of(&c->p), c->p.dtype, s4, c->p.N, c->P, c->S, wd, lam[0], part, kRedBlocks, A, c->stream);
+    launch_adj_seed(stencil_of(&c->p), c->p.dtype, s4, c->p.N, c->P, c->S[c->cur], wd, lam[0], part, kRedBlocks, A, c->stream);
     HIPCHK(hipGetLastError());
     // The reverse steps of segment s run on the context's stream while the
     // recompute of segment s - 1 runs on the auxiliary stream, into the other
@@ -1221,7 +1247,7 @@ int lf_spectrum(lf_ctx *c, int which, int nbins, double *power, double *count, v
                           c->stream);
     HIPCHK(hipGetLastError());
     DevScalars hs;
-    HIPCHK(hipMemcpyAsync(&hs, c->S, sizeof hs, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipMemcpyAsync(&hs, c->S[c->cur], sizeof hs, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     const double bg = vel ? hs.bg_v[fld] : hs.bg_f[fld] - h * hs.bg_v[fld];
     HIPCHK(hipMemcpyAsync(c->tot, &bg, sizeof bg, hipMemcpyHostToDevice, c->stream));
@@ -1377,8 +1403,9 @@ int lf_autotune(const lf_params *p, void *stream, void *workspace, size_t ws_byt
         lf_ctx *c = nullptr;
         if ((rc = lf_create(&cand[i], stream, workspace, ws_bytes, &c))) return rc;
         void *s4[4] = {c->buf[0][0], c->buf[0][1], c->buf[0][2], c->buf[0][3]};
-        launch_fill_synthetic(c->p.dtype, s4, c->p.N, c->S, c->stream);
-        launch_reduce(stencil_of(&c->p), c->p.dtype, s4[0], s4[1], c->p.N, c->S->bg_f, c->p.beta, c->part,
+        launch_fill_synthetic(c->p.dtype, s4, c->p.N, c->S[0], c->stream);
+        launch_set_powers(c->P, c->S[0], c->stream);
+        launch_reduce(stencil_of(&c->p), c->p.dtype, s4[0], s4[1], c->p.N, c->S[0]->bg_f, c->p.beta, c->part[0],
                       c->sh.rows, c->stream);
         c->inited = 1;
         c->cur = 0;
@@ -1586,11 +1613,13 @@ int lf_ens_create(int R, const lf_params *per, void *stream, void *workspace, si
         memset(&t, 0, sizeof t);
         for (int b = 0; b < 2; ++b)
             for (int j = 0; j < 4; ++j) t.buf[b][j] = c->buf[b][j];
-        t.part = c->part;
+        for (int b = 0; b < 2; ++b) {
+            t.part[b] = c->part[b];
+            t.S[b] = c->S[b];
+        }
         t.C = c->C;
         t.Cw = c->C;
         t.P = c->P;
-        t.S = c->S;
         t.N = q.N;
         t.zchunk = c->sh.zchunk;
         t.ntx = (q.N + c->sh.tile_x - 1) / c->sh.tile_x;
@@ -1682,7 +1711,7 @@ namespace {
 
 void ens_enqueue_step(lf_ens *e, int parity, hipStream_t st)
 {
-    launch_aupdate_ens(e->tab, e->R, e->queue, st);
+    launch_aupdate_ens(e->tab, e->R, e->queue, parity, st);
     launch_sweep_ens(e->stencil, e->dtype, e->tile_x, e->tile_y, e->beta, e->tab, e->items, e->nitems, e->queue,
                      e->grid, parity, st);
 }
@@ -1994,8 +2023,9 @@ int lf_ens_autotune(int R, const lf_params *per, void *stream, void *workspace, 
         for (int r = 0; r < R; ++r) {
             lf_ctx *c = e->sub[r];
             void *s4[4] = {c->buf[0][0], c->buf[0][1], c->buf[0][2], c->buf[0][3]};
-            launch_fill_synthetic(c->p.dtype, s4, c->p.N, c->S, c->stream);
-            launch_reduce(stencil_of(&c->p), c->p.dtype, s4[0], s4[1], c->p.N, c->S->bg_f, c->p.beta, c->part,
+            launch_fill_synthetic(c->p.dtype, s4, c->p.N, c->S[0], c->stream);
+            launch_set_powers(c->P, c->S[0], c->stream);
+            launch_reduce(stencil_of(&c->p), c->p.dtype, s4[0], s4[1], c->p.N, c->S[0]->bg_f, c->p.beta, c->part[0],
                           c->sh.rows, c->stream);
             c->inited = 1;
             c->cur = 0;

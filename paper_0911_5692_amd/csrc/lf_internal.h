@@ -13,6 +13,7 @@ constexpr int kNPart = 4;   // step reduction: sum|d+ f1|^2, sum|d+ f2|^2, sum f
 constexpr int kNMom = 10;   // input moments (see k_input_moments)
 constexpr int kNEn = 6;     // energy sums (see k_diag_march)
 constexpr int kStage2Threads = 256;
+constexpr int kNPow = 5;    // powers of a kept with the scalars (scale_power in lf_scale.h)
 
 // Model parameters in device memory (read by the scale-factor kernel, so a
 // captured graph picks up lf_set_coupling without re-capture).
@@ -38,7 +39,33 @@ struct DevScalars {
     unsigned int pad;
     // initialisation scratch
     double mean_f[2], mean_u[2], conv, ad0;
+    double pw[kNPow];   // powers of a_half that the next step needs (scale_power)
 };
+
+struct CoefPair;
+
+// Where a sweep takes its step's coefficients from.  With part == nullptr a
+// scale-factor kernel has written them to C.  Otherwise every block forms
+// them itself from the rows x kNPart partial sums at part, the scalars S and
+// the powers kept there, and one block also writes So, C and tape (if not
+// NULL): with `extra` a block of its own after those of the tiles, else the
+// block of the first tile.  S and So, and the rows read and written, are
+// different memory: blocks start and end at different times.
+struct StepSource {
+    const double *part;
+    int rows;
+    const DevParams *P;
+    const DevScalars *S;
+    DevScalars *So;
+    CoefPair *C;
+    DevScalars *tape;
+    int extra;
+};
+
+// Most rows a sweep sums in its own blocks.  Every block reads all of them
+// (rows^2 x 32 B over the launch), so above this the separate kernel's single
+// pass is the cheaper one.
+constexpr int kFusedRows = 1024;
 
 // Per-step coefficients of the fused kick-drift, written by the scale-factor
 // kernel in both precisions (the sweep reads its own).
@@ -82,10 +109,10 @@ __device__ inline int xcd_item(int round_base, int nitems)
 // One realization of an ensemble, as the batched kernels see it.
 struct EnsEntry {
     void *buf[2][4];        // ping/pong deviation arrays d1, d2, e1, e2
-    double *part;           // partial-sum rows of this realization
+    double *part[2];        // partial-sum rows by parity: a step reads one and writes the other
     const CoefPair *C;      // its per-step coefficients
     const DevParams *P;
-    DevScalars *S;
+    DevScalars *S[2];       // scalars by parity
     CoefPair *Cw;           // same as C, writable (scale-factor kernel)
     int N, zchunk, ntx, nty, rows, pad;
 };
@@ -100,12 +127,14 @@ void launch_init_fields(int dtype, int in_dtype, const void *f1, const void *f2,
                         const DevParams *P, const DevScalars *S, hipStream_t st);
 void launch_reduce(int stencil, int dtype, const void *d1, const void *d2, int N, const double *bg_f,
                    int beta, double *part, int nblk, hipStream_t st);
-// tape (may be NULL): receives a copy of *S as it was before the update
-void launch_aupdate(const double *part, int nblk, const DevParams *P, DevScalars *S,
+// tape (may be NULL): receives a copy of *S; So is not S
+void launch_aupdate(const double *part, int nblk, const DevParams *P, const DevScalars *S, DevScalars *So,
                     CoefPair *C, hipStream_t st, DevScalars *tape = nullptr);
+// the powers of a of scalars that did not come from a step or an initialisation
+void launch_set_powers(const DevParams *P, DevScalars *S, hipStream_t st);
 // queue: the ensemble sweep's work counters (8, 32 ints apart), reset to 0
 // by this kernel, followed by the 9 segment bounds of the item list
-void launch_aupdate_ens(const EnsEntry *tab, int R, int *queue, hipStream_t st);
+void launch_aupdate_ens(const EnsEntry *tab, int R, int *queue, int parity, hipStream_t st);
 void launch_sweep_ens(int stencil, int dtype, int tile_x, int tile_y, int beta, const EnsEntry *tab,
                       const int4 *items, int nitems, int *queue, int grid, int parity, hipStream_t st);
 void launch_sweep_plain(int stencil, int dtype, int beta, const void *const in[4], void *const out[4], int N,
@@ -121,7 +150,7 @@ struct SweepIO {
     int nz;
 };
 void launch_sweep_lds(int stencil, int dtype, int tile_x, int tile_y, int beta, const void *const in[4],
-                      void *const out[4], int N, int zchunk, const CoefPair *C, double *part,
+                      void *const out[4], int N, int zchunk, const StepSource &src, double *part,
                       hipStream_t st);
 // z-slab sweeps (lf_slab7.hip, lf_slab27.hip); launch_sweep_slab dispatches
 // to launch_sweep_slab27 for stencil 27
@@ -135,7 +164,7 @@ int sweep_io_blocks(int N, int nz, int tile_x, int tile_y, int zchunk);
 // 27-point LDS sweep (lf_sweep27.hip); launch_sweep_lds / launch_sweep_ens /
 // sweep_lds_blocks_per_cu dispatch to these for stencil 27.
 void launch_sweep_lds27(int dtype, int tile_x, int tile_y, int beta, const void *const in[4],
-                        void *const out[4], int N, int zchunk, const CoefPair *C, double *part,
+                        void *const out[4], int N, int zchunk, const StepSource &src, double *part,
                         hipStream_t st);
 void launch_sweep_ens27(int dtype, int tile_x, int tile_y, int beta, const EnsEntry *tab,
                         const int4 *items, int nitems, int *queue, int grid, int parity, hipStream_t st);

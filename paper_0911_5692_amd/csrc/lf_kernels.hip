@@ -4,6 +4,7 @@
 //
 // Equation references: Sainio, "CUDAEASY", arXiv:0911.5692, Sec. II.B.
 #include "lf_internal.h"
+#include "lf_scale.h"
 
 #include <math.h>
 
@@ -59,13 +60,6 @@ __device__ inline void stage2_sum(const double *part, int nblk, double (&tot)[NV
     for (int i = 0; i < NV; ++i) tot[i] = res[i];
 }
 
-__device__ inline double ipow_d(double x, int n)
-{
-    double r = 1.0;
-    for (int i = 0; i < n; ++i) r *= x;
-    return r;
-}
-
 // ---------------------------------------------------------------- init
 
 // Moments of an input state (element type Tin), FP64 per site:
@@ -105,7 +99,7 @@ __global__ void __launch_bounds__(kStage2Threads) k_init_scalars(const double *p
 {
     double m[kNMom];
     stage2_sum<kNMom>(part, nblk, m);
-    if (threadIdx.x != 0) return;
+    if (threadIdx.x >= 64) return;  // one wave, every lane alike; lane 0 writes
     const double N3 = P->N3, r = P->r, s = P->s;
     const double mf1 = m[0] / N3, mf2 = m[1] / N3, mu1 = m[2] / N3, mu2 = m[3] / N3;
     double conv = 0.0;
@@ -124,6 +118,9 @@ __global__ void __launch_bounds__(kStage2Threads) k_init_scalars(const double *p
     }
     const double vb1 = mu1 + conv * mf1, vb2 = mu2 + conv * mf2;
     const double h = 0.5 * P->dt;
+    const double pw = scale_power(threadIdx.x, P, a0 + h * ad0);
+    if (threadIdx.x < kNPow) S->pw[threadIdx.x] = pw;
+    if (threadIdx.x != 0) return;
     S->mean_f[0] = mf1; S->mean_f[1] = mf2;
     S->mean_u[0] = mu1; S->mean_u[1] = mu2;
     S->conv = conv;
@@ -206,105 +203,46 @@ __global__ void k_set_pending(double *part, int nblk, const double *tot)
 
 // ---------------------------------------------------------------- a-update
 
-__device__ inline double binom_d(int n, int k)
-{
-    double r = 1.0;
-    for (int i = 1; i <= k; ++i) r = r * (double)(n - k + i) / (double)i;
-    return r;
-}
-
-// One step of the scale factor and the homogeneous mode, in FP64, and the
-// coefficients of the fused kick-drift (eq. scale, eq. scalar-evo, eq. evo).
-// State on entry: a_{k+1/2}, a'_k, background f_bar(k+1/2), v_bar(k), and
-// the partial sums over f(k+1/2).
-//   F_a = kappa^2 a^(-2s-2r-1) [Sg/3 + a^(2s+2) SV]
-//   a'_{k+1} solves a'_{k+1} = a'_k + dt[(-s-2)((a'_k + a'_{k+1})/2)^2/a + F_a]
-//     (time-centred; the root that tends to a'_k + dt F_a as the quadratic
-//      coefficient vanishes, written in the cancellation-free form)
-//   a'_{k+1/2} = (a'_k + a'_{k+1})/2, a''_{k+1/2} = (a'_{k+1} - a'_k)/dt,
-//   a_{k+3/2} = a_{k+1/2} + dt a'_{k+1}.
-__device__ void aupdate_block(const double *part, int nblk, const DevParams *__restrict__ P,
-                              DevScalars *S, CoefPair *C, DevScalars *tape)
+// One step of the scale factor and the homogeneous mode, and the coefficients
+// of the fused kick-drift (lf_scale.h), by one block.  The sweeps of a lone
+// lattice do this in their own blocks (CoefsOfStep in lf_sweep_common.h); this
+// is for launch shapes with many partial rows, the plain sweep and ensembles.
+__device__ void aupdate_block(const double *part, int nblk, const DevParams *__restrict__ P, const DevScalars *S,
+                              DevScalars *So, CoefPair *C, DevScalars *tape)
 {
     double t[kNPart];
     stage2_sum<kNPart>(part, nblk, t);
     if (threadIdx.x >= 64) return;
-    const double N3 = P->N3, dx = P->dx, dt = P->dt, r = P->r, s = P->s;
-    const double c1 = P->c1, G = P->G;
     const int beta = P->beta;
-    const double a = S->a_half, w = S->ad;
-    // the five powers of a, one per lane of the first wave, side by side
-    // instead of one after another on a single thread
-    const int l = threadIdx.x;
-    const double ex = l == 0 ? P->p1 : l == 1 ? P->p2 : l == 2 ? -2.0 * s - 2.0 * r - 1.0
-                    : l == 3 ? 2.0 * s + 2.0 : -2.0 * s - 2.0;
-    const double pw = pow(a, ex);
-    const double ap1 = __shfl(pw, 0, 64), ap2 = __shfl(pw, 1, 64), aF = __shfl(pw, 2, 64);
-    const double aV = __shfl(pw, 3, 64), alpha = __shfl(pw, 4, 64);
-    if (l != 0) return;
-    if (tape) *tape = *S;  // the scalars before this step (the adjoint's tape)
-    const double Sg = P->gw * (t[0] + t[1]) / (dx * dx * N3);
-    const double SV = (c1 * ap1 * t[2] / (double)beta + 0.5 * G * ap2 * t[3]) / N3;
-    const double Fa = P->kappa2 * aF * (Sg / 3.0 + aV * SV);
-    const double c = (-s - 2.0) * dt / (4.0 * a);
-    const double disc = 1.0 - 8.0 * c * w - 4.0 * c * dt * Fa;
-    const double u = 2.0 * (c * w * w + w + dt * Fa) / ((1.0 - 2.0 * c * w) + sqrt(disc));
-    const double adh = 0.5 * (w + u), add = (u - w) / dt, an = a + dt * u;
-    const double bc = r * (s - r + 2.0) * (adh / a) * (adh / a) + r * add / a;
-
-    // homogeneous mode: same kick and drift with zero Laplacian
-    const double g1 = S->bg_f[0], g2 = S->bg_f[1];
-    const double dV1 = c1 * ap1 * ipow_d(g1, beta - 1) + G * ap2 * g1 * g2 * g2;
-    const double dV2 = G * ap2 * g1 * g1 * g2;
-    const double vb1 = S->bg_v[0] + dt * (bc * g1 - dV1);
-    const double vb2 = S->bg_v[1] + dt * (bc * g2 - dV2);
-    const double g1n = g1 + dt * vb1, g2n = g2 + dt * vb2;
-
-    // coefficients at k+1/2
-    double h[kMaxBeta];
-    for (int j = 0; j < kMaxBeta; ++j) h[j] = 0.0;
-    for (int j = 1; j <= beta - 1; ++j)
-        h[j - 1] = dt * c1 * ap1 * binom_d(beta - 1, j) * ipow_d(g1, beta - 1 - j);
-    const double Cl = dt * alpha * P->gw / (dx * dx), Cf = dt * bc, C2 = dt * G * ap2;
-    Coef<double> &cd = C->d;
-    Coef<float> &cf = C->f;
-    cd.Cl = Cl; cd.Cf = Cf; cd.dt = dt; cd.C2 = C2; cd.g1 = g1; cd.g2 = g2;
-    cd.two_g1 = 2.0 * g1; cd.two_g2 = 2.0 * g2; cd.g1sq = g1 * g1; cd.nh = beta - 1;
-    cf.Cl = (float)Cl; cf.Cf = (float)Cf; cf.dt = (float)dt; cf.C2 = (float)C2;
-    cf.g1 = (float)g1; cf.g2 = (float)g2; cf.two_g1 = (float)(2.0 * g1);
-    cf.two_g2 = (float)(2.0 * g2); cf.g1sq = (float)(g1 * g1); cf.nh = beta - 1;
-    for (int j = 0; j < kMaxBeta; ++j) { cd.h[j] = h[j]; cf.h[j] = (float)h[j]; }
-    C->g1n = g1n;
-    C->g2n = g2n;
-
-    unsigned int bad = 0;
-    for (int i = 0; i < kNPart; ++i) bad |= !isfinite(t[i]);
-    bad |= !(disc >= 0.0) || !isfinite(u);
-    S->status |= bad;
-    for (int i = 0; i < kNPart; ++i) S->pend[i] = t[i];
-    S->a_half = an;
-    S->ad = u;
-    S->bg_f[0] = g1n; S->bg_f[1] = g2n;
-    S->bg_v[0] = vb1; S->bg_v[1] = vb2;
-    S->step += 1;
+    ScaleStep o;
+    scale_step(t, ScaleIn(P, S), beta, o);
+    if (threadIdx.x == 0) scale_commit(t, o, P, S, So, C, tape, beta);
+    scale_commit_powers(o.an, P, So);
 }
 
 __global__ void __launch_bounds__(kStage2Threads) k_aupdate(const double *part, int nblk,
                                                             const DevParams *__restrict__ P,
-                                                            DevScalars *S, CoefPair *C, DevScalars *tape)
+                                                            const DevScalars *S, DevScalars *So, CoefPair *C,
+                                                            DevScalars *tape)
 {
-    aupdate_block(part, nblk, P, S, C, tape);
+    aupdate_block(part, nblk, P, S, So, C, tape);
+}
+
+__global__ void __launch_bounds__(64) k_set_powers(const DevParams *__restrict__ P, DevScalars *S)
+{
+    const double pw = scale_power(threadIdx.x, P, S->a_half);
+    if (threadIdx.x < kNPow) S->pw[threadIdx.x] = pw;
 }
 
 // Ensemble: block r updates realization r.
-__global__ void __launch_bounds__(kStage2Threads) k_aupdate_ens(const EnsEntry *tab, int *queue)
+__global__ void __launch_bounds__(kStage2Threads) k_aupdate_ens(const EnsEntry *tab, int *queue, int parity)
 {
     // the sweep that follows takes its work items from these counters (one
     // per XCD, 32 ints apart)
     if (blockIdx.x == 0 && threadIdx.x < 8)
         __hip_atomic_store(queue + 32 * threadIdx.x, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const EnsEntry &e = tab[blockIdx.x];
-    aupdate_block(e.part, e.rows, e.P, e.S, e.Cw, nullptr);
+    aupdate_block(e.part[parity], e.rows, e.P, e.S[parity], e.S[parity ^ 1], e.Cw, nullptr);
 }
 
 // ---------------------------------------------------------------- energies
@@ -693,15 +631,20 @@ void launch_reduce(int stencil, int dtype, const void *d1, const void *d2, int N
     }
 }
 
-void launch_aupdate(const double *part, int nblk, const DevParams *P, DevScalars *S, CoefPair *C,
-                    hipStream_t st, DevScalars *tape)
+void launch_aupdate(const double *part, int nblk, const DevParams *P, const DevScalars *S, DevScalars *So,
+                    CoefPair *C, hipStream_t st, DevScalars *tape)
 {
-    hipLaunchKernelGGL(k_aupdate, dim3(1), dim3(kStage2Threads), 0, st, part, nblk, P, S, C, tape);
+    hipLaunchKernelGGL(k_aupdate, dim3(1), dim3(kStage2Threads), 0, st, part, nblk, P, S, So, C, tape);
 }
 
-void launch_aupdate_ens(const EnsEntry *tab, int R, int *queue, hipStream_t st)
+void launch_set_powers(const DevParams *P, DevScalars *S, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_aupdate_ens, dim3(R), dim3(kStage2Threads), 0, st, tab, queue);
+    hipLaunchKernelGGL(k_set_powers, dim3(1), dim3(64), 0, st, P, S);
+}
+
+void launch_aupdate_ens(const EnsEntry *tab, int R, int *queue, int parity, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_aupdate_ens, dim3(R), dim3(kStage2Threads), 0, st, tab, queue, parity);
 }
 
 // Launch shape of k_diag_march for an N^3 lattice: tiles of 64 x DY, z-chunks

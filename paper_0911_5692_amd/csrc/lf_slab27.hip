@@ -18,7 +18,7 @@ __global__ void __launch_bounds__(256, LF_SWEEP27_WAVES(T)) k_sweep_slab27(
     const int tz = b / nty;
     const int z0 = tz * zchunk;
     sweep_tile27<T, NH, TX, TY, true>(d1, d2, e1, e2, d1n, d2n, e1n, e2n, N, zp, tx * TX, ty * TY, z0,
-                                      min(z0 + zchunk, zp.nz), C, part + (size_t)tile * kNPart);
+                                      min(z0 + zchunk, zp.nz), CoefsFrom{C}, part + (size_t)tile * kNPart);
 }
 
 namespace {

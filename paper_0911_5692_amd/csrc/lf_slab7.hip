@@ -23,7 +23,7 @@ __global__ void __launch_bounds__(256, LF_SWEEP_MIN_WAVES) k_sweep_slab(
     const int tz = b / nty;
     const int z0 = tz * zchunk;
     sweep_tile<T, NH, TX, TY, LF_SWEEP_PREFETCH, true>(d1, d2, e1, e2, d1n, d2n, e1n, e2n, N, zp, tx * TX,
-                                                       ty * TY, z0, min(z0 + zchunk, zp.nz), C,
+                                                       ty * TY, z0, min(z0 + zchunk, zp.nz), CoefsFrom{C},
                                                        part + (size_t)tile * kNPart);
 }
 

@@ -95,16 +95,21 @@ template <typename T, int NH, int TX, int TY>
 __global__ void __launch_bounds__(256, LF_SWEEP_MIN_WAVES) k_sweep_lds(
     const T *__restrict__ d1, const T *__restrict__ d2, const T *__restrict__ e1, const T *__restrict__ e2,
     T *__restrict__ d1n, T *__restrict__ d2n, T *__restrict__ e1n, T *__restrict__ e2n, const int N,
-    const int zchunk, const int ntx, const int nty, const CoefPair *__restrict__ C, double *__restrict__ part)
+    const int zchunk, const int ntx, const int nty, const StepSource src, double *__restrict__ part)
 {
     // partial row = logical tile index (the ensemble kernel uses the same rows)
-    const int tile = xcd_remap(blockIdx.x, gridDim.x);
+    const int ntiles = gridDim.x - src.extra;
+    if ((int)blockIdx.x == ntiles) {
+        step_extra_block(src);
+        return;
+    }
+    const int tile = xcd_remap(blockIdx.x, ntiles);
     const int tx = tile % ntx, b = tile / ntx;
     const int ty = b % nty;
     const int tz = b / nty;
     const int z0 = tz * zchunk;
     sweep_tile<T, NH, TX, TY, LF_SWEEP_PREFETCH, false>(d1, d2, e1, e2, d1n, d2n, e1n, e2n, N, ZPlanes<T>{},
-                                                        tx * TX, ty * TY, z0, min(z0 + zchunk, N), C,
+                                                        tx * TX, ty * TY, z0, min(z0 + zchunk, N), CoefsOfStep(src, !src.extra && tile == 0),
                                                         part + (size_t)tile * kNPart);
 }
 
@@ -126,8 +131,8 @@ __global__ void __launch_bounds__(256, LF_SWEEP_MIN_WAVES) k_sweep_ens(
         T *const *out = (T *const *)e.buf[parity ^ 1];
         sweep_tile<T, NH, TX, TY, LF_SWEEP_PREFETCH, false>(in[0], in[1], in[2], in[3], out[0], out[1], out[2],
                                                             out[3], e.N, ZPlanes<T>{}, tx * TX, ty * TY, z0,
-                                                            min(z0 + e.zchunk, e.N), e.C,
-                                                            e.part + (size_t)it.z * kNPart);
+                                                            min(z0 + e.zchunk, e.N), CoefsFrom{e.C},
+                                                            e.part[parity ^ 1] + (size_t)it.z * kNPart);
     });
 }
 
@@ -180,46 +185,46 @@ int sweep_io_blocks(int N, int nz, int tile_x, int tile_y, int zchunk)
 
 template <typename T, int NH, int TX, int TY>
 static void sweep_lds_t(const void *const in[4], void *const out[4], int N, int zchunk,
-                        const CoefPair *C, double *part, hipStream_t st)
+                        const StepSource &src, double *part, hipStream_t st)
 {
     const int ntx = (N + TX - 1) / TX, nty = (N + TY - 1) / TY, nzc = (N + zchunk - 1) / zchunk;
-    hipLaunchKernelGGL((k_sweep_lds<T, NH, TX, TY>), dim3(ntx * nty * nzc), dim3(256), 0, st,
+    hipLaunchKernelGGL((k_sweep_lds<T, NH, TX, TY>), dim3(ntx * nty * nzc + src.extra), dim3(256), 0, st,
                        (const T *)in[0], (const T *)in[1], (const T *)in[2], (const T *)in[3],
-                       (T *)out[0], (T *)out[1], (T *)out[2], (T *)out[3], N, zchunk, ntx, nty, C, part);
+                       (T *)out[0], (T *)out[1], (T *)out[2], (T *)out[3], N, zchunk, ntx, nty, src, part);
 }
 
 template <typename T, int TX, int TY>
 static void sweep_lds_b(int beta, const void *const in[4], void *const out[4], int N, int zchunk,
-                        const CoefPair *C, double *part, hipStream_t st)
+                        const StepSource &src, double *part, hipStream_t st)
 {
     switch (beta) {
-    case 2: sweep_lds_t<T, 1, TX, TY>(in, out, N, zchunk, C, part, st); break;
-    case 3: sweep_lds_t<T, 2, TX, TY>(in, out, N, zchunk, C, part, st); break;
-    case 4: sweep_lds_t<T, 3, TX, TY>(in, out, N, zchunk, C, part, st); break;
-    case 5: sweep_lds_t<T, 4, TX, TY>(in, out, N, zchunk, C, part, st); break;
-    default: sweep_lds_t<T, 5, TX, TY>(in, out, N, zchunk, C, part, st); break;
+    case 2: sweep_lds_t<T, 1, TX, TY>(in, out, N, zchunk, src, part, st); break;
+    case 3: sweep_lds_t<T, 2, TX, TY>(in, out, N, zchunk, src, part, st); break;
+    case 4: sweep_lds_t<T, 3, TX, TY>(in, out, N, zchunk, src, part, st); break;
+    case 5: sweep_lds_t<T, 4, TX, TY>(in, out, N, zchunk, src, part, st); break;
+    default: sweep_lds_t<T, 5, TX, TY>(in, out, N, zchunk, src, part, st); break;
     }
 }
 
 // Supported tiles (x by y): 32x8, 32x16, 64x4, 64x8, 64x16, 128x4, 128x8.
 template <typename T>
 static void sweep_lds_y(int tile_x, int tile_y, int beta, const void *const in[4], void *const out[4],
-                        int N, int zchunk, const CoefPair *C, double *part, hipStream_t st)
+                        int N, int zchunk, const StepSource &src, double *part, hipStream_t st)
 {
     if (tile_x == 128) {
-        if (tile_y == 4) sweep_lds_b<T, 128, 4>(beta, in, out, N, zchunk, C, part, st);
-        else sweep_lds_b<T, 128, 8>(beta, in, out, N, zchunk, C, part, st);
+        if (tile_y == 4) sweep_lds_b<T, 128, 4>(beta, in, out, N, zchunk, src, part, st);
+        else sweep_lds_b<T, 128, 8>(beta, in, out, N, zchunk, src, part, st);
         return;
     }
     if (tile_x == 32) {
-        if (tile_y == 8) sweep_lds_b<T, 32, 8>(beta, in, out, N, zchunk, C, part, st);
-        else sweep_lds_b<T, 32, 16>(beta, in, out, N, zchunk, C, part, st);
+        if (tile_y == 8) sweep_lds_b<T, 32, 8>(beta, in, out, N, zchunk, src, part, st);
+        else sweep_lds_b<T, 32, 16>(beta, in, out, N, zchunk, src, part, st);
         return;
     }
     switch (tile_y) {
-    case 4: sweep_lds_b<T, 64, 4>(beta, in, out, N, zchunk, C, part, st); break;
-    case 8: sweep_lds_b<T, 64, 8>(beta, in, out, N, zchunk, C, part, st); break;
-    default: sweep_lds_b<T, 64, 16>(beta, in, out, N, zchunk, C, part, st); break;
+    case 4: sweep_lds_b<T, 64, 4>(beta, in, out, N, zchunk, src, part, st); break;
+    case 8: sweep_lds_b<T, 64, 8>(beta, in, out, N, zchunk, src, part, st); break;
+    default: sweep_lds_b<T, 64, 16>(beta, in, out, N, zchunk, src, part, st); break;
     }
 }
 
@@ -308,12 +313,12 @@ void launch_sweep_ens(int stencil, int dtype, int tile_x, int tile_y, int beta, 
 }
 
 void launch_sweep_lds(int stencil, int dtype, int tile_x, int tile_y, int beta, const void *const in[4],
-                      void *const out[4], int N, int zchunk, const CoefPair *C, double *part,
+                      void *const out[4], int N, int zchunk, const StepSource &src, double *part,
                       hipStream_t st)
 {
-    if (stencil == 27) launch_sweep_lds27(dtype, tile_x, tile_y, beta, in, out, N, zchunk, C, part, st);
-    else if (dtype == 0) sweep_lds_y<float>(tile_x, tile_y, beta, in, out, N, zchunk, C, part, st);
-    else sweep_lds_y<double>(tile_x, tile_y, beta, in, out, N, zchunk, C, part, st);
+    if (stencil == 27) launch_sweep_lds27(dtype, tile_x, tile_y, beta, in, out, N, zchunk, src, part, st);
+    else if (dtype == 0) sweep_lds_y<float>(tile_x, tile_y, beta, in, out, N, zchunk, src, part, st);
+    else sweep_lds_y<double>(tile_x, tile_y, beta, in, out, N, zchunk, src, part, st);
 }
 
 }  // namespace lf

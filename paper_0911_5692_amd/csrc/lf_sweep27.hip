@@ -51,15 +51,20 @@ template <typename T, int NH, int TX, int TY>
 __global__ void __launch_bounds__(256, LF_SWEEP27_WAVES(T)) k_sweep_lds27(
     const T *__restrict__ d1, const T *__restrict__ d2, const T *__restrict__ e1, const T *__restrict__ e2,
     T *__restrict__ d1n, T *__restrict__ d2n, T *__restrict__ e1n, T *__restrict__ e2n, const int N,
-    const int zchunk, const int ntx, const int nty, const CoefPair *__restrict__ C, double *__restrict__ part)
+    const int zchunk, const int ntx, const int nty, const StepSource src, double *__restrict__ part)
 {
-    const int tile = xcd_remap(blockIdx.x, gridDim.x);
+    const int ntiles = gridDim.x - src.extra;
+    if ((int)blockIdx.x == ntiles) {
+        step_extra_block(src);
+        return;
+    }
+    const int tile = xcd_remap(blockIdx.x, ntiles);
     const int tx = tile % ntx, b = tile / ntx;
     const int ty = b % nty;
     const int tz = b / nty;
     const int z0 = tz * zchunk;
     sweep_tile27<T, NH, TX, TY, false>(d1, d2, e1, e2, d1n, d2n, e1n, e2n, N, ZPlanes<T>{}, tx * TX, ty * TY,
-                                       z0, min(z0 + zchunk, N), C, part + (size_t)tile * kNPart);
+                                       z0, min(z0 + zchunk, N), CoefsOfStep(src, !src.extra && tile == 0), part + (size_t)tile * kNPart);
 }
 
 template <typename T, int NH, int TX, int TY>
@@ -75,8 +80,8 @@ __global__ void __launch_bounds__(256, LF_SWEEP27_WAVES(T)) k_sweep_ens27(
         const T *const *in = (const T *const *)e.buf[parity];
         T *const *out = (T *const *)e.buf[parity ^ 1];
         sweep_tile27<T, NH, TX, TY, false>(in[0], in[1], in[2], in[3], out[0], out[1], out[2], out[3], e.N,
-                                           ZPlanes<T>{}, tx * TX, ty * TY, z0, min(z0 + e.zchunk, e.N), e.C,
-                                           e.part + (size_t)it.z * kNPart);
+                                           ZPlanes<T>{}, tx * TX, ty * TY, z0, min(z0 + e.zchunk, e.N), CoefsFrom{e.C},
+                                           e.part[parity ^ 1] + (size_t)it.z * kNPart);
     });
 }
 
@@ -86,16 +91,16 @@ namespace {
 
 template <typename T>
 void lds27_t(int tile_x, int tile_y, int beta, const void *const in[4], void *const out[4], int N,
-             int zchunk, const CoefPair *C, double *part, hipStream_t st)
+             int zchunk, const StepSource &src, double *part, hipStream_t st)
 {
     with_tile(tile_x, tile_y, [&](auto tx, auto ty) {
         constexpr int TX = decltype(tx)::value, TY = decltype(ty)::value;
         with_nh(beta, [&](auto nh) {
             constexpr int NH = decltype(nh)::value;
             const int ntx = (N + TX - 1) / TX, nty = (N + TY - 1) / TY, nzc = (N + zchunk - 1) / zchunk;
-            hipLaunchKernelGGL((k_sweep_lds27<T, NH, TX, TY>), dim3(ntx * nty * nzc), dim3(256), 0, st,
+            hipLaunchKernelGGL((k_sweep_lds27<T, NH, TX, TY>), dim3(ntx * nty * nzc + src.extra), dim3(256), 0, st,
                                (const T *)in[0], (const T *)in[1], (const T *)in[2], (const T *)in[3],
-                               (T *)out[0], (T *)out[1], (T *)out[2], (T *)out[3], N, zchunk, ntx, nty, C,
+                               (T *)out[0], (T *)out[1], (T *)out[2], (T *)out[3], N, zchunk, ntx, nty, src,
                                part);
         });
     });
@@ -133,11 +138,11 @@ int occ27_t(int tile_x, int tile_y, int beta)
 }  // namespace
 
 void launch_sweep_lds27(int dtype, int tile_x, int tile_y, int beta, const void *const in[4],
-                        void *const out[4], int N, int zchunk, const CoefPair *C, double *part,
+                        void *const out[4], int N, int zchunk, const StepSource &src, double *part,
                         hipStream_t st)
 {
-    if (dtype == 0) lds27_t<float>(tile_x, tile_y, beta, in, out, N, zchunk, C, part, st);
-    else lds27_t<double>(tile_x, tile_y, beta, in, out, N, zchunk, C, part, st);
+    if (dtype == 0) lds27_t<float>(tile_x, tile_y, beta, in, out, N, zchunk, src, part, st);
+    else lds27_t<double>(tile_x, tile_y, beta, in, out, N, zchunk, src, part, st);
 }
 
 void launch_sweep_ens27(int dtype, int tile_x, int tile_y, int beta, const EnsEntry *tab,

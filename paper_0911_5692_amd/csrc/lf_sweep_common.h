@@ -4,6 +4,7 @@
 // background, and the XCD-aware block order.
 #pragma once
 #include "lf_internal.h"
+#include "lf_scale.h"
 
 namespace lf {
 
@@ -72,6 +73,132 @@ __device__ inline double potential_pow(double x)
     for (int j = 0; j < NH; ++j) r *= x;  // x^(NH+1) = x^beta
     return r;
 }
+
+// The step's coefficients as a scale-factor kernel left them.
+struct CoefsFrom {
+    const CoefPair *__restrict__ C;
+    template <typename T, int NH>
+    __device__ inline void get(Coefs<T, NH> &c, double &g1n, double &g2n) const
+    {
+        c.load(coef_of<T>(C));
+        g1n = C->g1n;
+        g2n = C->g2n;
+    }
+    __device__ inline void finish() const {}
+};
+
+// The totals of a step's partial rows, formed by a whole block of 256 threads
+// and the same in every thread.  The rows are added in the order of the
+// scale-factor kernel (thread, wave, block), so both give the same bits.
+__device__ inline void step_totals(const StepSource &q, const ScaleIn &in, double (&tot)[kNPart])
+{
+    static_assert(kStage2Threads == 256, "rows are dealt to the threads as in stage 2");
+    __shared__ double sm[kNPart][4];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    // all of the thread's rows in flight at once
+    constexpr int kRows = kFusedRows / 256;
+    double row[kRows][kNPart];
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+        const int j = t + 256 * k;
+#pragma unroll
+        for (int i = 0; i < kNPart; ++i) row[k][i] = j < q.rows ? q.part[(size_t)j * kNPart + i] : 0.0;
+    }
+    in.arrived();
+#pragma unroll
+    for (int i = 0; i < kNPart; ++i) {
+        double x = 0.0;
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) x += row[k][i];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+        if (lane == 0) sm[i][w] = x;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kNPart; ++i) {
+        tot[i] = 0.0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) tot[i] += sm[i][v];
+    }
+}
+
+// Writes what a fused step leaves besides the arrays; first wave of a block.
+__device__ inline void step_commit(const StepSource &q, const double (&tot)[kNPart], const ScaleStep &o)
+{
+    if (threadIdx.x == 0) scale_commit(tot, o, q.P, q.S, q.So, q.C, q.tape, in_const(q.P)->beta);
+    scale_commit_powers(o.an, q.P, q.So);
+}
+
+// The extra block of a fused step (StepSource::extra).
+__device__ inline void step_extra_block(const StepSource &q)
+{
+    const ScaleIn in(q.P, q.S);
+    double tot[kNPart];
+    step_totals(q, in, tot);
+    if (threadIdx.x >= 64) return;
+    ScaleStep o;
+    scale_step(tot, in, in_const(q.P)->beta, o);
+    step_commit(q, tot, o);
+}
+
+// The step's coefficients formed in this block (StepSource), or read from C
+// when a scale-factor kernel ran.  A kernel of its own for this chain of
+// dependent FP64 operations on one block takes 5 to 6 us between two sweeps
+// in which the device does nothing else; in every block of the sweep it
+// takes about 3.  Step times, two kernels against one: 32^3 FP64 10.8 ->
+// 8.8 us, 128^3 FP32 25.6 -> 23.8, 256^3 114.3 -> 110.9, 512^3 792 -> 789
+// (7 points).  `first`: this block writes the results.
+struct CoefsOfStep {
+    const StepSource &q;
+    const bool first;
+    __device__ inline CoefsOfStep(const StepSource &src, bool f) : q(src), first(f) {}
+    template <typename T, int NH>
+    __device__ inline void get(Coefs<T, NH> &c, double &g1n, double &g2n) const
+    {
+        if (!q.part) {
+            CoefsFrom{q.C}.template get<T, NH>(c, g1n, g2n);
+            return;
+        }
+        const ScaleIn in(q.P, q.S);
+        double tot[kNPart];
+        step_totals(q, in, tot);
+        ScaleStep o;
+        scale_step(tot, in, NH + 1, o);
+        const double g1 = in.g1, g2 = in.g2;
+        c.Cl = uniform((T)o.Cl); c.Cf = uniform((T)o.Cf); c.dt = (T)in.dt; c.C2 = uniform((T)o.C2);
+        c.g1 = (T)g1; c.g2 = (T)g2;
+        c.two_g1 = uniform((T)(2.0 * g1)); c.two_g2 = uniform((T)(2.0 * g2)); c.g1sq = uniform((T)(g1 * g1));
+#pragma unroll
+        for (int j = 0; j < NH; ++j) c.h[j] = uniform((T)scale_h(o.ch, NH + 1, j + 1, g1));
+        g1n = uniform(o.g1n);
+        g2n = uniform(o.g2n);
+        if (first && threadIdx.x == 0) {
+            StepResult &r = result();
+#pragma unroll
+            for (int i = 0; i < kNPart; ++i) r.t[i] = tot[i];
+            r.o = o;
+        }
+    }
+    // The results are written when the march is over: the stores and pow
+    // among the first loads would set the kernel's register count.
+    __device__ inline void finish() const
+    {
+        if (!q.part || !first || threadIdx.x >= 64) return;
+        step_commit(q, result().t, result().o);
+    }
+
+private:
+    struct StepResult {
+        double t[kNPart];
+        ScaleStep o;
+    };
+    __device__ static inline StepResult &result()
+    {
+        __shared__ StepResult r;
+        return r;
+    }
+};
 
 // Where the z-planes of the four input arrays (d1, d2, e1, e2) of a z-slab
 // sweep lie.  A sweep reads d on planes [z0-2, z1] and e on [z0-1, z1-1] of
