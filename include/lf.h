@@ -95,12 +95,12 @@ typedef struct lf_params {
     double kappa2;    /* 8 pi G_Newton / A^2 (0 = no expansion) */
     int32_t tile_y;   /* sweep tile rows: 0 = automatic, 1 = plain one-site-per-thread
                          sweep with a separate reduction, 4, 8 or 16 = LDS z-march */
-    int32_t zchunk;   /* planes per z-chunk of the LDS sweep, 0 = automatic (a grid that
-                         is resident at once: two blocks per CU for FP32 sweeps with
-                         128-wide tiles, else as many as fit, with chunks of at most
-                         64 planes) */
-    int32_t tile_x;   /* sweep tile columns: 0 = automatic (128 x 8 from N = 256 up,
-                         64 x 8 or 64 x 4 below), 32, 64 or 128 (128 with tile_y 4 or
+    int32_t zchunk;   /* planes per z-chunk of the LDS sweep, 0 = automatic (for the tile, the
+                         cut of the lattice into at most one, two, four or eight blocks per
+                         CU with the least estimated step time) */
+    int32_t tile_x;   /* sweep tile columns: 0 = automatic (with tile_y 0: the tile with the
+                         least estimated step time for this N, dtype and stencil, 128 x 8 in
+                         FP32 at 256 and 512; else 64), 32, 64 or 128 (128 with tile_y 4 or
                          8 only; 32 with tile_y 8 or 16 and the 7-point stencil only) */
     int32_t stencil;  /* Laplacian: 0 or 7 = 7-point, 27 = 27-point (see above) */
 } lf_params;

@@ -59,14 +59,6 @@ struct Shape {
     int tile_x, tile_y, zchunk, rows;  // rows: partial-sum rows the step reduction writes
 };
 
-// Automatic launch shape.  Tiles of 128 x 8 from N = 256 (both stencils),
-// narrower ones below.  The z-chunk is chosen so that the whole grid is
-// resident at once (resident blocks = blocks per CU from the occupancy
-// calculator x CU count): all tiles then march their chunks in lockstep and
-// the halo rows a tile shares with its neighbours are still in L2 when they
-// are needed (see auto_zchunk).  The resident count is only queried on a
-// machine with a GPU; elsewhere (and for the workspace size) 3 blocks on 256
-// CUs is assumed, which only changes the partial-sum row count.
 // 7 or 27 (lf_params.stencil 0 means 7).
 int stencil_of(const lf_params *p) { return p->stencil == 27 ? 27 : 7; }
 
@@ -88,27 +80,94 @@ int resident_blocks(const lf_params *p, int tile_x, int tile_y)
     return per_cu * cu_count();
 }
 
-// Automatic z-chunk of an LDS sweep over nz planes of N x N (N = p->N).
-// The whole grid resident at once (tiles march in lockstep and find their
-// neighbours' halo lines in L2).  The FP32 sweeps with 128-wide tiles do best
-// with two blocks per CU: a smaller L2 working set per XCD and long chunks
-// (7 points at 512^3: 256 planes, fetch 1.03x the algorithmic reads against
-// 1.16x with three blocks per CU and 64 planes; 256^3: 32 planes; 27 points:
-// 6% faster at 512^3 and 11% at 256^3 than 64-wide tiles filling the CUs).
-// The other sweeps fill the CUs and keep chunks of at most 64 planes.
+// Automatic launch shape of the LDS sweeps.
+//
+// A sweep's time is that of one round of blocks: every block marches its
+// z-chunk plane by plane, all blocks side by side, so tiles stay in step and
+// find their neighbours' halo rows in L2.  Two blocks per CU are enough to
+// keep the memory busy (a third only enlarges the L2 working set: 512^3 FP32,
+// fetch 1.16x the algorithmic reads against 1.03x), and a second round costs
+// as much as the first however few blocks it has.  So each tile is cut into
+// as many z-chunks as give at most one or two blocks per CU (or four or
+// eight, in rounds, for lattices whose tile columns fit neither well), and
+// the shape with the least (planes + start-up planes) x cost of a plane is
+// taken.  The cost of a plane (a block of that tile, two blocks per CU; 64x8
+// = 1) and the other constants are fitted to step times of every tile at 34
+// sizes from 20^3 to 448^3: the choice is within 1% of the fastest shape on
+// average and within 14% at worst (300^3 FP32, 27 points).  The rule
+// before it (tiles by N alone, chunks of 8 to 64 planes filling all resident
+// blocks) was 17% (FP32, 27 points) to 30% (FP64, 7 points) off: 32^3 FP64
+// 16.6 -> 7.9 us a step, 128^3 FP32 26.8 -> 22.9, 200^3 FP32 88.1 -> 66.3,
+// 320^3 FP64 666 -> 430; 256^3 and 512^3 FP32 keep their shapes.
+struct TileCost {
+    int tx, ty;
+    double plane;
+};
+struct ShapeModel {
+    TileCost tile[5];    // tiles of the class, unused entries 0
+    double start;        // start-up of a block, in planes
+    double lone, rounds; // factor of a plane at one block per CU; of each further round
+};
+
+const ShapeModel &shape_model(int dtype, int stencil)
+{
+    static const ShapeModel f32_7 = {
+        {{128, 8, 0.83}, {128, 4, 0.64}, {64, 8, 1.0}, {32, 16, 0.60}, {32, 8, 0.50}}, 3, 0.79, 2.67};
+    static const ShapeModel f32_27 = {
+        {{128, 8, 1.57}, {64, 16, 1.65}, {64, 8, 1.0}, {64, 4, 0.65}, {0, 0, 0}}, 3, 0.79, 1.09};
+    static const ShapeModel f64_7 = {
+        {{128, 4, 0.92}, {64, 8, 1.0}, {64, 4, 1.02}, {32, 8, 0.68}, {0, 0, 0}}, 1, 0.64, 1.18};
+    static const ShapeModel f64_27 = {{{64, 8, 1.0}, {64, 4, 0.53}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, 6, 0.65, 1.0};
+    return dtype == LF_F64 ? (stencil == 27 ? f64_27 : f64_7) : (stencil == 27 ? f32_27 : f32_7);
+}
+
+// Best z-chunk of tile_x x tile_y over nz planes of N x N, and its cost for
+// a plane cost of 1.
+int best_zchunk(const lf_params *p, int tile_x, int tile_y, int nz, double *cost)
+{
+    const ShapeModel &m = shape_model(p->dtype, stencil_of(p));
+    const int cus = cu_count();
+    int per_cu = sweep_lds_blocks_per_cu(stencil_of(p), p->dtype, tile_x, tile_y, p->beta);
+    (void)hipGetLastError();
+    const long long round = (long long)cus * (per_cu == 1 ? 1 : 2);
+    const long long cols = (long long)((p->N + tile_x - 1) / tile_x) * ((p->N + tile_y - 1) / tile_y);
+    int best = nz;
+    *cost = 1e300;
+    for (long long cap = cus; cap <= 8LL * cus; cap *= 2) {
+        long long k = cap / cols;
+        k = k < 1 ? 1 : (k > nz ? nz : k);
+        const int z = (int)((nz + k - 1) / k);
+        const long long nb = cols * ((nz + z - 1) / z), r = (nb + round - 1) / round;
+        const double c = (z + m.start) * (r > 1 ? (double)r * m.rounds : nb <= cus ? m.lone : 1.0);
+        if (c < *cost) {
+            *cost = c;
+            best = z;
+        }
+    }
+    return best;
+}
+
 int auto_zchunk(const lf_params *p, int tile_x, int tile_y, int nz)
 {
-    const int N = p->N;
-    const bool two_per_cu = p->dtype == LF_F32 && tile_x == 128;
-    const int per_slab = ((N + tile_x - 1) / tile_x) * ((N + tile_y - 1) / tile_y);
-    const int res = resident_blocks(p, tile_x, tile_y);
-    const int target = two_per_cu && 2 * cu_count() < res ? 2 * cu_count() : res;
-    int nzc = target / per_slab;
-    nzc = nzc < 1 ? 1 : nzc;
-    int dz = (nz + nzc - 1) / nzc;
-    const int dz_max = two_per_cu ? nz : 64;
-    dz = dz < 8 ? 8 : (dz > dz_max ? dz_max : dz);
-    return dz < nz ? dz : nz;
+    double cost;
+    return best_zchunk(p, tile_x, tile_y, nz, &cost);
+}
+
+void auto_shape(const lf_params *p, int *tile_x, int *tile_y, int *zchunk)
+{
+    const ShapeModel &m = shape_model(p->dtype, stencil_of(p));
+    double best = 1e300;
+    for (const TileCost &t : m.tile) {
+        if (!t.tx) continue;
+        double c;
+        const int z = best_zchunk(p, t.tx, t.ty, p->N, &c);
+        if (c * t.plane < best) {
+            best = c * t.plane;
+            *tile_x = t.tx;
+            *tile_y = t.ty;
+            *zchunk = z;
+        }
+    }
 }
 
 Shape shape_of(const lf_params *p)
@@ -118,12 +177,8 @@ Shape shape_of(const lf_params *p)
     if (p->tile_y) {
         sh.tile_y = p->tile_y;
         sh.tile_x = p->tile_x ? p->tile_x : 64;
-    } else if (N >= 256) {
-        sh.tile_x = 128;
-        sh.tile_y = 8;
     } else {
-        sh.tile_x = 64;
-        sh.tile_y = N >= 96 ? 8 : 4;
+        auto_shape(p, &sh.tile_x, &sh.tile_y, &sh.zchunk);
     }
     if (sh.tile_y == 1) {
         sh.tile_x = 0;
@@ -131,7 +186,8 @@ Shape shape_of(const lf_params *p)
         sh.rows = kRedBlocks;
         return sh;
     }
-    sh.zchunk = p->zchunk ? (p->zchunk < N ? p->zchunk : N) : auto_zchunk(p, sh.tile_x, sh.tile_y, N);
+    if (p->zchunk) sh.zchunk = p->zchunk < N ? p->zchunk : N;
+    else if (p->tile_y) sh.zchunk = auto_zchunk(p, sh.tile_x, sh.tile_y, N);
     sh.rows = sweep_lds_blocks(N, sh.tile_x, sh.tile_y, sh.zchunk);
     return sh;
 }
