@@ -401,7 +401,7 @@ int lf_time_kernels(lf_ctx *ctx, int64_t n, double *ms, int n_out);
 
 /* ---- vacuum initial state on the device (Sec. II.B) --------------------
  * The homogeneous values are inputs; the fluctuations are generated through
- * an FFT, as the paper does after DEFROST (hipFFT in place of CUFFT):
+ * an FFT, as the paper does after DEFROST (own passes or hipFFT in place of CUFFT):
  *   f_i = f0_i + F_i,  u_i = u0_i + U_i  (program units; u are the rescaled
  *   physical velocities that lf_init_physical takes),
  * with F_i, U_i independent Gaussian random fields of power spectrum
@@ -424,11 +424,12 @@ typedef struct lf_vacuum {
     uint64_t seed;    /* generator key */
 } lf_vacuum;
 
-/* Scratch for lf_vacuum_fields: the half spectrum of one array
- * (N^2 (N/2+1) complex doubles) plus the FFT work area.  Needs a device (the
- * FFT plans are made to size their work area).  The hipFFT plans of each
- * (device, N) are made once per process and kept; they hold small tables of
- * their own but no work area. */
+/* Scratch for lf_vacuum_fields: the half spectrum of one array (N^2 rows of
+ * N/2+1 complex doubles, padded) plus a table or the FFT work area.  N from 96
+ * whose prime factors are at most 7 are transformed in this library's own
+ * passes; other N through hipFFT, whose plans need a device to size their
+ * work area, are made once per process and (device, N) and kept, and hold
+ * small tables of their own but no work area. */
 int lf_vacuum_workspace_bytes(const lf_params *p, size_t *out_bytes);
 /* Generate f1, f2, u1, u2 (FP64 device arrays of N^3, 256-byte aligned,
  * caller-owned) for the lattice of p on `stream`.  The large buffers come
@@ -459,8 +460,10 @@ int lf_init_vacuum(lf_ctx *ctx, const lf_vacuum *v, double a0, void *workspace, 
 /* Shells that hold every mode of an N^3 lattice: rint(sqrt(3) (N div 2)) + 1
  * (returns the count, 0 for N < 1). */
 int lf_spectrum_bins(int N);
-/* Device scratch for lf_spectrum (one FP64 field, the half spectrum, the FFT
- * work area and per-plane partial sums).  Needs a device. */
+/* Device scratch for lf_spectrum: the half spectrum and partial sums, and for
+ * N that are not powers of two from 128 (transformed through hipFFT, see
+ * lf_vacuum_workspace_bytes) one FP64 field and the FFT work area.  Needs a
+ * device. */
 int lf_spectrum_workspace_bytes(const lf_params *p, size_t *out_bytes);
 /* power, count: HOST arrays of nbins doubles, 1 <= nbins <= lf_spectrum_bins(N)
  * (shells >= nbins are left out).  Blocking. */

@@ -1277,7 +1277,7 @@ int lf_spectrum_workspace_bytes(const lf_params *p, size_t *out_bytes)
     char msg[256];
     size_t b = 0;
     if (spectrum_workspace_bytes(p->N, &b, msg, sizeof msg)) return fail(LF_EHIP, "%s", msg);
-    *out_bytes = vac_array_bytes(p->N) + b;
+    *out_bytes = b;
     return LF_OK;
 }
 
@@ -1292,24 +1292,12 @@ int lf_spectrum(lf_ctx *c, int which, int nbins, double *power, double *count, v
     int rc;
     if ((rc = check_ptr(workspace, "workspace"))) return rc;
     if (!c->inited) return fail(LF_ESTATE, "lf_spectrum before lf_init");
-    const size_t arr = vac_array_bytes(c->p.N);
-    if (ws_bytes < arr) return fail(LF_ENOMEM, "workspace of %zu bytes is smaller than one array", ws_bytes);
-    // the synchronised deviation of field `which` and, in the scalar slot,
-    // its homogeneous value (background at time k)
-    double *dev = (double *)workspace;
+    // the synchronised deviation of field `which` is formed on the way
     const int fld = which & 1, vel = which >> 1;
-    const double h = 0.5 * c->p.dt;
-    launch_sync_deviation(c->p.dtype, c->buf[c->cur][fld], c->buf[c->cur][2 + fld], dev, c->p.N, h, vel,
-                          c->stream);
-    HIPCHK(hipGetLastError());
-    DevScalars hs;
-    HIPCHK(hipMemcpyAsync(&hs, c->S[c->cur], sizeof hs, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    const double bg = vel ? hs.bg_v[fld] : hs.bg_f[fld] - h * hs.bg_v[fld];
-    HIPCHK(hipMemcpyAsync(c->tot, &bg, sizeof bg, hipMemcpyHostToDevice, c->stream));
     char msg[256];
-    const int e = spectrum_compute(c->p.N, c->p.L, dev, c->tot, nbins, c->stream, (char *)workspace + arr,
-                                   ws_bytes - arr, power, count, msg, sizeof msg);
+    const int e = spectrum_compute(c->p.N, c->p.L, c->p.dtype, c->buf[c->cur][fld], c->buf[c->cur][2 + fld],
+                                   c->S[c->cur], fld, vel, 0.5 * c->p.dt, nbins, c->stream, workspace, ws_bytes,
+                                   power, count, msg, sizeof msg);
     if (e) return fail(e == 2 ? LF_ENOMEM : LF_EHIP, "%s", msg);
     return LF_OK;
 }

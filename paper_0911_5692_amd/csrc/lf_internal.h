@@ -219,9 +219,10 @@ int vacuum_generate(int N, double L, const struct ::lf_vacuum *v, hipStream_t st
                     double *const out[4], char *msg, size_t len);
 int spectrum_bins(int N);
 int spectrum_workspace_bytes(int N, size_t *bytes, char *msg, size_t len);
-// power, count: host arrays of nbins; dev: FP64 device array N^3 holding the
-// deviation from the homogeneous value bg (device scalar), which enters shell 0
-int spectrum_compute(int N, double L, double *dev, const double *bg, int nbins, hipStream_t st, void *ws,
-                     size_t ws_bytes, double *power, double *count, char *msg, size_t len);
+// Spectrum of field fld (0, 1) or its velocity from the stored arrays d, e and
+// the scalars S; h = dt/2.  power, count: host arrays of nbins.
+int spectrum_compute(int N, double L, int dtype, const void *d, const void *e, const DevScalars *S, int fld,
+                     int velocity, double h, int nbins, hipStream_t st, void *ws, size_t ws_bytes, double *power,
+                     double *count, char *msg, size_t len);
 
 }  // namespace lf
