@@ -121,15 +121,24 @@ const ShapeModel &shape_model(int dtype, int stencil)
     return dtype == LF_F64 ? (stencil == 27 ? f64_27 : f64_7) : (stencil == 27 ? f32_27 : f32_7);
 }
 
+// LDS of a sweep block: two staged planes and two of new values for 7 points,
+// three of each for 27 (lf_sweep_tile.h, lf_sweep27_tile.h), both fields.
+constexpr int kLdsOfCu = 160 * 1024;
+
+int tile_lds(const lf_params *p, int tile_x, int tile_y)
+{
+    const int es = p->dtype == LF_F64 ? 8 : 4;
+    if (stencil_of(p) == 27) return 6 * es * ((tile_x + 4) * (tile_y + 3) + (tile_x + 2) * (tile_y + 1));
+    return 4 * es * ((tile_x + 3) * (tile_y + 3) + (tile_x + 1) * (tile_y + 1));
+}
+
 // Best z-chunk of tile_x x tile_y over nz planes of N x N, and its cost for
 // a plane cost of 1.
 int best_zchunk(const lf_params *p, int tile_x, int tile_y, int nz, double *cost)
 {
     const ShapeModel &m = shape_model(p->dtype, stencil_of(p));
     const int cus = cu_count();
-    int per_cu = sweep_lds_blocks_per_cu(stencil_of(p), p->dtype, tile_x, tile_y, p->beta);
-    (void)hipGetLastError();
-    const long long round = (long long)cus * (per_cu == 1 ? 1 : 2);
+    const long long round = (long long)cus * (2 * tile_lds(p, tile_x, tile_y) > kLdsOfCu ? 1 : 2);
     const long long cols = (long long)((p->N + tile_x - 1) / tile_x) * ((p->N + tile_y - 1) / tile_y);
     int best = nz;
     *cost = 1e300;
@@ -1506,32 +1515,67 @@ constexpr int kEnsQueueInts = kXcdCount * 32 + kXcdCount + 1;
 int ens_tile_y(const lf_params *p0) { return p0->tile_y ? p0->tile_y : 8; }
 int ens_tile_x(const lf_params *p0) { return p0->tile_x ? p0->tile_x : 64; }
 
+// z-chunk of an N-plane lattice for a target item length: the fewest equal
+// chunks of at most `target` planes (0 = the ensemble's default rule).
+int ens_zchunk_for(int N, int target)
+{
+    if (target <= 0 || target >= N) return target <= 0 ? 0 : N;
+    const int n = (N + target - 1) / target;
+    return (N + n - 1) / n;
+}
+
+// Default target item length of an ensemble.  The items (a tile column's
+// z-chunk) of all realizations are dealt to the resident blocks.  A single
+// round of at most two items per CU lasts as long as its longest item; with
+// more items the blocks share the CUs and the step lasts about the planes of
+// all items, start-up planes included, over two blocks per CU (a plane takes
+// less of the time of a lone round then), plus most of a last item while the
+// others have run out.  The target with the least of this is taken; the
+// constants are fitted to 19 ensembles of 2 to 68 lattices of 25^3 to 160^3,
+// where the choice is within 2% of the best target on average.  Step times
+// against chunks of half a lattice, the rule before (64 x 8 tiles): 15
+// lattices of 64^3 to 160^3 134 -> 92 us, the 68 of the ensemble workload 401
+// -> 316, two of 100^3 81 -> 38, the 15 in FP64 226 -> 153, with 27 points
+// 192 -> 120.
+int ens_target(int R, const lf_params *per)
+{
+    static const struct { double factor, tail, start; } model[2][2] = {
+        {{0.8, 0.8, 2.0}, {0.8, 0.6, 10.0}}, {{0.7, 0.8, 8.0}, {0.7, 0.8, 8.0}}};  // [dtype][27 points]
+    static const int targets[15] = {2, 4, 6, 8, 12, 16, 20, 24, 32, 40, 48, 64, 96, 128, 192};
+    const auto &m = model[per[0].dtype == LF_F64][stencil_of(&per[0]) == 27];
+    const int tx = ens_tile_x(&per[0]), ty = ens_tile_y(&per[0]);
+    const double slots = 2.0 * cu_count();
+    int best = 1;
+    double least = 1e300;
+    for (int t : targets) {
+        long long items = 0, planes = 0;
+        int longest = 0;
+        for (int r = 0; r < R; ++r) {
+            const int N = per[r].N, z = per[r].zchunk ? (per[r].zchunk < N ? per[r].zchunk : N) : ens_zchunk_for(N, t);
+            const long long cols = (long long)((N + tx - 1) / tx) * ((N + ty - 1) / ty);
+            items += cols * ((N + z - 1) / z);
+            planes += cols * N;
+            longest = z > longest ? z : longest;
+        }
+        const double c = items <= slots ? longest + m.start
+                                        : m.factor * ((planes + m.start * items) / slots + m.tail * longest);
+        if (c < least) {
+            least = c;
+            best = t;
+        }
+    }
+    return best;
+}
+
 // Parameters of realization r as its sub-context sees them: the ensemble's
-// common tile, and unless given a z-chunk of half the lattice (at least 8
-// planes): two chunks per tile column.  On gfx950 that beat 16-64-plane
-// chunks for the mixed 64^3..160^3 ensemble by 5-8%, the fewer chunk-boundary
-// planes outweighing the smaller work list.
-// Default z-chunk of a realization: the whole lattice (one item per tile
-// column) when the ensemble's tile columns fill between half and all of the
-// resident grid, so that every item runs in a single round; otherwise half
-// the lattice (at least 8 planes).
-lf_params ens_sub_params(const lf_params *pr, const lf_params *p0, bool full_z)
+// common tile and, unless given, the z-chunk of the default target.
+lf_params ens_sub_params(const lf_params *pr, const lf_params *p0, int target)
 {
     lf_params q = *pr;
     q.tile_x = ens_tile_x(p0);
     q.tile_y = ens_tile_y(p0);
-    if (!q.zchunk) q.zchunk = full_z ? pr->N : (pr->N / 2 > 8 ? pr->N / 2 : (pr->N < 8 ? pr->N : 8));
+    if (!q.zchunk) q.zchunk = ens_zchunk_for(pr->N, target);
     return q;
-}
-
-bool ens_full_z(int R, const lf_params *per)
-{
-    const int tx = ens_tile_x(&per[0]), ty = ens_tile_y(&per[0]);
-    long long cols = 0;
-    for (int r = 0; r < R; ++r) cols += (long long)((per[r].N + tx - 1) / tx) * ((per[r].N + ty - 1) / ty);
-    const lf_params q0 = ens_sub_params(&per[0], &per[0], false);
-    const long long grid = resident_blocks(&q0, tx, ty);
-    return 2 * cols >= grid && cols <= grid;
 }
 
 int ens_validate(int R, const lf_params *per)
@@ -1555,9 +1599,9 @@ size_t ens_layout(int R, const lf_params *per, size_t *sub_off, int *nitems)
 {
     size_t off = 0;
     int items = 0;
-    const bool full_z = ens_full_z(R, per);
+    const int target = ens_target(R, per);
     for (int r = 0; r < R; ++r) {
-        lf_params q = ens_sub_params(&per[r], &per[0], full_z);
+        lf_params q = ens_sub_params(&per[r], &per[0], target);
         sub_off[r] = off;
         off = align_up(off + layout_of(&q).total);
         Shape sh = shape_of(&q);
@@ -1646,9 +1690,9 @@ int lf_ens_create(int R, const lf_params *per, void *stream, void *workspace, si
     EnsEntry *htab = new EnsEntry[R];
     int4 *hitems = new int4[nitems > 0 ? nitems : 1];
     int k = 0;
-    const bool full_z = ens_full_z(R, per);
+    const int target = ens_target(R, per);
     for (int r = 0; r < R && rc == LF_OK; ++r) {
-        lf_params q = ens_sub_params(&per[r], &per[0], full_z);
+        lf_params q = ens_sub_params(&per[r], &per[0], target);
         rc = lf_create(&q, stream, ws + so[r], so[r + 1] - so[r], &e->sub[r]);
         if (rc) break;
         lf_ctx *c = e->sub[r];
@@ -1738,7 +1782,7 @@ int lf_ens_create(int R, const lf_params *per, void *stream, void *workspace, si
         return rc;
     }
     // persistent grid: as many blocks as fit on the device at once
-    const lf_params q0 = ens_sub_params(&per[0], &per[0], false);
+    const lf_params q0 = ens_sub_params(&per[0], &per[0], 8);
     int res = resident_blocks(&q0, e->tile_x, e->tile_y);
     e->grid = nitems < res ? nitems : res;
     if ((rc = ens_prepare_graphs(e))) {
@@ -1896,15 +1940,6 @@ int lf_ens_get_fields(lf_ens *e, int r, void *f1, void *f2, void *v1, void *v2, 
 // ---------------------------------------------------------------- ensemble autotuner
 
 namespace {
-
-// z-chunk of an N-plane lattice for a target item length: the fewest equal
-// chunks of at most `target` planes (0 = the ensemble's default rule).
-int ens_zchunk_for(int N, int target)
-{
-    if (target <= 0 || target >= N) return target <= 0 ? 0 : N;
-    const int n = (N + target - 1) / target;
-    return (N + n - 1) / n;
-}
 
 // Cache key of an ensemble: the multiset of lattice sizes, "N:count,..." in
 // increasing N.  Returns 0 if it does not fit in `len` characters.
