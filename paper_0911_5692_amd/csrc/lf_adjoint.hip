@@ -16,6 +16,10 @@
 //           since it is the Dirichlet form of the same Laplacian); inside a
 //           segment of stored states it also forms pass A of the next
 //           reverse step.
+// Between reverse steps the cotangents are kept as lambda_f and mu =
+// lambda_v + dt lambda_f (of the state the last step left): the next step
+// needs mu at every stencil neighbour and lambda_f at the site alone, so the
+// halo of a tile is half of what lambda_v and lambda_f would make it.
 // Cotangent arrays are FP64 whatever the state precision; stored states are
 // deviations from the FP64 background and are turned back into full fields
 // f = f_bar + d in FP64 on the fly.
@@ -77,7 +81,7 @@ __device__ inline double ipw(double x, int n)
 
 // Cotangent of E = sum_i wK_i K_i + wG_i G_i at the synchronised time of
 // the state (d, e; background and scale factor in S), written to lam[0..3]
-// (lambda_f1, lambda_f2, lambda_v1, lambda_v2), plus the per-block sums the
+// (lambda_f1, lambda_f2, mu1, mu2), plus the per-block sums the
 // scalar part needs: sum q1^2, sum q2^2, the raw gradient sums of fs1 and fs2,
 // sum_i wK_i q_i fs_i.
 template <typename T, int ST>
@@ -85,7 +89,7 @@ __global__ void __launch_bounds__(256) k_adj_seed(const T *__restrict__ d1, cons
                                                   const T *__restrict__ e1, const T *__restrict__ e2,
                                                   int N, const DevParams *__restrict__ P,
                                                   const DevScalars *__restrict__ S, const double *__restrict__ w,
-                                                  double *lf1, double *lf2, double *lv1, double *lv2,
+                                                  double *lf1, double *lf2, double *mu1, double *mu2,
                                                   double *part)
 {
     const int64_t N3 = (int64_t)N * N * N;
@@ -118,8 +122,9 @@ __global__ void __launch_bounds__(256) k_adj_seed(const T *__restrict__ d1, cons
         const double dfs2 = -r * hub * dq2 - 2.0 * wG2 * gfac * lap2 / n3;
         lf1[i] = dfs1;
         lf2[i] = dfs2;
-        lv1[i] = dq1 - h * dfs1;
-        lv2[i] = dq2 - h * dfs2;
+        // lambda_v = dq - h dfs, mu = lambda_v + 2 h lambda_f
+        mu1[i] = dq1 + h * dfs1;
+        mu2[i] = dq2 + h * dfs2;
         acc[0] += q1 * q1;
         acc[1] += q2 * q2;
         acc[2] += grad_raw<ST>(sy1, c1v);
@@ -156,7 +161,7 @@ __global__ void __launch_bounds__(256) k_adj_seed_scalar(const double *part, int
 // ------------------------------------------------------------ reverse step
 
 // Pass A: sums over the stored fields f = f_bar + d at k+1/2 and
-// mu = lambda_v' + dt lambda_f' (cotangent of v(k+1)):
+// mu (cotangent of v(k+1)):
 //  0: sum mu_i S(f_i)   1: sum mu_i f_i   2: sum mu1 f1 f2^2 + mu2 f1^2 f2
 //  3: sum mu1 f1^(beta-1)   4: sum f1^beta   5: sum f1^2 f2^2
 //  6: raw gradient sums of f_1 plus f_2
@@ -164,9 +169,8 @@ __global__ void __launch_bounds__(256) k_adj_seed_scalar(const double *part, int
 template <typename T, int ST>
 __global__ void __launch_bounds__(256) k_adj_reduce(const T *__restrict__ d1, const T *__restrict__ d2,
                                                     int N, int beta, const DevScalars *__restrict__ tape,
-                                                    const double *__restrict__ lf1, const double *__restrict__ lf2,
-                                                    const double *__restrict__ lv1, const double *__restrict__ lv2,
-                                                    double dt, double *part)
+                                                    const double *__restrict__ m1, const double *__restrict__ m2,
+                                                    double *part)
 {
     const int64_t N3 = (int64_t)N * N * N;
     const double g1 = tape->bg_f[0], g2 = tape->bg_f[1];
@@ -180,7 +184,7 @@ __global__ void __launch_bounds__(256) k_adj_reduce(const T *__restrict__ d1, co
         const double f1 = g1 + a1, f2 = g2 + a2;
         const double s1 = lap_raw<ST, double>(v1, a1);
         const double s2 = lap_raw<ST, double>(v2, a2);
-        const double mu1 = lv1[i] + dt * lf1[i], mu2 = lv2[i] + dt * lf2[i];
+        const double mu1 = m1[i], mu2 = m2[i];
         acc[0] += mu1 * s1 + mu2 * s2;
         acc[1] += mu1 * f1 + mu2 * f2;
         acc[2] += mu1 * f1 * f2 * f2 + mu2 * f1 * f1 * f2;
@@ -281,8 +285,8 @@ __global__ void __launch_bounds__(256) k_adj_scalar(const double *part, int nblk
 // NEXT also pass A of the next reverse step (X_{k-1}: stored fields n1, n2,
 // scalars tape_n) over the cotangents just written, into part.
 //
-// It needs, per site, mu = lambda_v' + dt lambda_f' and the stored d (and n)
-// at every stencil neighbour in planes z-1, z, z+1.  A block owns a 64 x 4
+// It needs, per site, lambda_f, and mu and the stored d (and n) at every
+// stencil neighbour in planes z-1, z, z+1.  A block owns a 64 x 4
 // column tile and marches z over a chunk: the three planes sit in LDS with a
 // one-cell ring (four buffers, so one barrier per plane), and plane z+2 is
 // loaded into registers while plane z is evaluated.  The grid walks a static
@@ -313,8 +317,8 @@ __global__ void __launch_bounds__(256) k_adj_fields(const T *__restrict__ d1, co
                                                     int N, int beta, const DevScalars *__restrict__ tape,
                                                     const double *__restrict__ cf,
                                                     const double *__restrict__ lf1, const double *__restrict__ lf2,
-                                                    const double *__restrict__ lv1, const double *__restrict__ lv2,
-                                                    double *of1, double *of2, double *ov1, double *ov2,
+                                                    const double *__restrict__ mi1, const double *__restrict__ mi2,
+                                                    double *of1, double *of2, double *om1, double *om2,
                                                     const T *__restrict__ n1, const T *__restrict__ n2,
                                                     const DevScalars *__restrict__ tape_n, double *part,
                                                     int zchunk, int ntx, int nty, int nitems)
@@ -353,29 +357,29 @@ __global__ void __launch_bounds__(256) k_adj_fields(const T *__restrict__ d1, co
         const int roff = wrap(y0 + ry) * N + wrap(x0 + rx);
 
         // the plane in flight, site and ring cell
-        double pf1, pf2, pv1, pv2, hf1 = 0, hf2 = 0, hv1 = 0, hv2 = 0;
+        double pf1, pf2, pm1, pm2, hm1 = 0, hm2 = 0;
         T pd1, pd2, hd1 = 0, hd2 = 0, pn1 = 0, pn2 = 0, hn1 = 0, hn2 = 0;
         auto load = [&](int z) {
             const int64_t o = zoff(z) + off;
-            pf1 = lf1[o]; pf2 = lf2[o]; pv1 = lv1[o]; pv2 = lv2[o];
+            pf1 = lf1[o]; pf2 = lf2[o]; pm1 = mi1[o]; pm2 = mi2[o];
             pd1 = d1[o]; pd2 = d2[o];
             if (NEXT) { pn1 = n1[o]; pn2 = n2[o]; }
             if (hasr) {
                 const int64_t h = zoff(z) + roff;
-                hf1 = lf1[h]; hf2 = lf2[h]; hv1 = lv1[h]; hv2 = lv2[h];
+                hm1 = mi1[h]; hm2 = mi2[h];
                 hd1 = d1[h]; hd2 = d2[h];
                 if (NEXT) { hn1 = n1[h]; hn2 = n2[h]; }
             }
         };
         auto stage = [&](int b) {
-            MU(b, 0)[slot] = pv1 + dt * pf1;
-            MU(b, 1)[slot] = pv2 + dt * pf2;
+            MU(b, 0)[slot] = pm1;
+            MU(b, 1)[slot] = pm2;
             FL(b, 0)[slot] = pd1;
             FL(b, 1)[slot] = pd2;
             if (NEXT) { FL(b, 2)[slot] = pn1; FL(b, 3)[slot] = pn2; }
             if (hasr) {
-                MU(b, 0)[rslot] = hv1 + dt * hf1;
-                MU(b, 1)[rslot] = hv2 + dt * hf2;
+                MU(b, 0)[rslot] = hm1;
+                MU(b, 1)[rslot] = hm2;
                 FL(b, 0)[rslot] = hd1;
                 FL(b, 1)[rslot] = hd2;
                 if (NEXT) { FL(b, 2)[rslot] = hn1; FL(b, 3)[rslot] = hn2; }
@@ -417,19 +421,20 @@ __global__ void __launch_bounds__(256) k_adj_fields(const T *__restrict__ d1, co
                 const double o1 = lc1 + cl * lm1 + cb * m1 - dt * (h11 * m1 + h12 * m2) + cSg * s1 + cSV * dv1;
                 const double o2 = lc2 + cl * lm2 + cb * m2 - dt * (h12 * m1 + h22 * m2) + cSg * s2 + cSV * dv2;
                 const int64_t i = (int64_t)z * NN + off;
+                // lambda_v of X_k is m: mu of the next reverse step
+                const double nu1 = m1 + dt * o1, nu2 = m2 + dt * o2;
                 of1[i] = o1;
                 of2[i] = o2;
-                ov1[i] = m1;
-                ov2[i] = m2;
+                om1[i] = nu1;
+                om2[i] = nu2;
                 if (NEXT) {
-                    // the terms of k_adj_reduce for X_{k-1}, with lambda = (o, m)
+                    // the terms of k_adj_reduce for X_{k-1}
                     auto w1 = [&](int dx, int dy, int dz) { return (double)FL(pick(dz), 2)[slot + dy * kALW + dx]; };
                     auto w2 = [&](int dx, int dy, int dz) { return (double)FL(pick(dz), 3)[slot + dy * kALW + dx]; };
                     const double b1 = (double)FL(bc, 2)[slot], b2 = (double)FL(bc, 3)[slot];
                     const double f1n = gn1 + b1, f2n = gn2 + b2;
                     const double t1 = lap_raw<ST, double>(w1, b1);
                     const double t2 = lap_raw<ST, double>(w2, b2);
-                    const double nu1 = m1 + dt * o1, nu2 = m2 + dt * o2;
                     acc[0] += nu1 * t1 + nu2 * t2;
                     acc[1] += nu1 * f1n + nu2 * f2n;
                     acc[2] += nu1 * f1n * f2n * f2n + nu2 * f1n * f1n * f2n;
@@ -446,17 +451,24 @@ __global__ void __launch_bounds__(256) k_adj_fields(const T *__restrict__ d1, co
     if (NEXT) bsum<7>(acc, part + (size_t)blockIdx.x * 7);
 }
 
-// Transpose of the desynchronisation f(1/2) = f(0) + dt/2 v(0) (in place on
-// the v cotangents) and of a_{1/2} = a0 + dt/2 a'0 (A[1] += dt/2 A[0]).
-__global__ void __launch_bounds__(256) k_adj_desync(int64_t N3, double h, const double *lf1,
-                                                    const double *lf2, double *lv1, double *lv2, double *A)
+// Transpose of the desynchronisation f(1/2) = f(0) + h v(0), h = dt/2, written
+// to the caller's arrays: the v cotangent is lambda_v + h lambda_f = mu - h
+// lambda_f; and of a_{1/2} = a0 + h a'0 (A[1] += h A[0]).
+__global__ void __launch_bounds__(256) k_adj_desync(int64_t N3, double h, const double *__restrict__ lf1,
+                                                    const double *__restrict__ lf2, const double *__restrict__ mu1,
+                                                    const double *__restrict__ mu2, double *__restrict__ gf1,
+                                                    double *__restrict__ gf2, double *__restrict__ gv1,
+                                                    double *__restrict__ gv2, double *A)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N3;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        lv1[i] += h * lf1[i];
-        lv2[i] += h * lf2[i];
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < N3) {
+        const double a = lf1[i], b = lf2[i];
+        gf1[i] = a;
+        gf2[i] = b;
+        gv1[i] = mu1[i] - h * a;
+        gv2[i] = mu2[i] - h * b;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) A[1] += h * A[0];
+    if (i == 0) A[1] += h * A[0];
 }
 
 // ------------------------------------------------------------ launchers
@@ -519,7 +531,7 @@ static void adj_step_t(const AdjStep &a, int N, int beta, const DevParams *P, do
     int rows = g.grid;
     if (!a.have_sums) {
         hipLaunchKernelGGL((k_adj_reduce<T, ST>), dim3(nblk), dim3(256), 0, st, (const T *)a.d1, (const T *)a.d2,
-                           N, beta, a.tape, a.lin[0], a.lin[1], a.lin[2], a.lin[3], dt, part);
+                           N, beta, a.tape, a.lin[2], a.lin[3], part);
         rows = nblk;
     }
     hipLaunchKernelGGL(k_adj_scalar, dim3(1), dim3(256), 0, st, part, rows, P, a.tape, A, cf);
@@ -554,12 +566,11 @@ void launch_adj_step(int stencil, int dtype, const AdjStep &a, int N, int beta, 
     }
 }
 
-void launch_adj_desync(int N, double dt, double *const lam[4], double *A, hipStream_t st)
+void launch_adj_desync(int N, double dt, double *const lam[4], double *const grad[4], double *A, hipStream_t st)
 {
     const int64_t N3 = (int64_t)N * N * N;
-    int64_t g = (N3 + 255) / 256;
-    hipLaunchKernelGGL(k_adj_desync, dim3((int)(g > 65536 ? 65536 : g)), dim3(256), 0, st, N3, 0.5 * dt,
-                       lam[0], lam[1], lam[2], lam[3], A);
+    hipLaunchKernelGGL(k_adj_desync, dim3((unsigned)((N3 + 255) / 256)), dim3(256), 0, st, N3, 0.5 * dt, lam[0], lam[1],
+                       lam[2], lam[3], grad[0], grad[1], grad[2], grad[3], A);
 }
 
 }  // namespace lf

@@ -1186,9 +1186,9 @@ int lf_adj_backward(lf_ctx *c, double dL, double *dL_dG, void *g_f1, void *g_f2,
     for (int i = 0; i < 5; ++i)
         if (ev[i]) (void)hipEventDestroy(ev[i]);
     if (rc) return rc;
-    launch_adj_desync(c->p.N, c->p.dt, lam[li], A, c->stream);
-    for (int j = 0; j < 4; ++j)
-        HIPCHK(hipMemcpyAsync(go[j], lam[li][j], n3 * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
+    double *grad[4] = {(double *)g_f1, (double *)g_f2, (double *)g_v1, (double *)g_v2};
+    launch_adj_desync(c->p.N, c->p.dt, lam[li], grad, A, c->stream);
+    HIPCHK(hipGetLastError());
     double hA[4];
     HIPCHK(hipMemcpyAsync(hA, A, sizeof hA, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));

@@ -191,7 +191,7 @@ void launch_adj_seed(int stencil, int dtype, const void *const s4[4], int N, con
                      const double *w, double *const lam[4], double *part, int nblk, double *A,
                      hipStream_t st);
 // One reverse step: stored fields d1, d2 and scalars tape of X_k, cotangents
-// lin (of X_{k+1}) -> lout (of X_k).  have_sums: part already holds the
+// lin (of X_{k+1}) -> lout (of X_k), each lambda_f1, lambda_f2, mu1, mu2.  have_sums: part already holds the
 // step's sums (formed by the previous step's fields pass).  next_*: when set,
 // the fields pass also forms the sums of the next reverse step (X_{k-1}).
 struct AdjStep {
@@ -205,7 +205,9 @@ struct AdjStep {
 };
 void launch_adj_step(int stencil, int dtype, const AdjStep &a, int N, int beta, const DevParams *P, double dt,
                      double *part, int nblk, double *A, double *cf, hipStream_t st);
-void launch_adj_desync(int N, double dt, double *const lam[4], double *A, hipStream_t st);
+// the cotangents (lambda_f, mu) of X_0 as gradients with respect to the
+// synchronised state, into grad[4]
+void launch_adj_desync(int N, double dt, double *const lam[4], double *const grad[4], double *A, hipStream_t st);
 void launch_set_pending(double *part, int nblk, const double *totals, hipStream_t st);
 }  // namespace lf
 
