@@ -290,12 +290,13 @@ struct lf_ctx {
     CoefPair *C;
     int extra;          // StepSource::extra of its sweeps
     int inited;
-    // g[j][p]: 2^j steps from buffer parity p, j = 0 .. logK (K = 2^logK
-    // steps per long graph).  An n-step call launches n div K long graphs and
-    // one graph per set bit of n mod K.
-    hipGraphExec_t g[kMaxLogK + 1][2];
+    // g[j]: 2^j steps from buffer parity 0, j = 0 .. logK (K = 2^logK steps per
+    // long graph); g1: one step from parity 1.  An n-step call first returns to
+    // parity 0, then launches n div K long graphs and one graph per set bit of
+    // n mod K.
+    hipGraphExec_t g[kMaxLogK + 1], g1;
     int logK;
-    int graphs_ready;   // every g[j][p] instantiated and uploaded
+    int graphs_ready;   // every graph instantiated and uploaded
     int ens_member;     // stepped by an ensemble: its own graphs are never used
     hipEvent_t ev0, ev1;
     int timed;
@@ -399,25 +400,21 @@ int capture(lf_ctx *c, int nsteps, int start, hipGraphExec_t *exec)
     return LF_OK;
 }
 
-// The graph of 2^j steps from parity p, captured on first use.
-int ensure_graph(lf_ctx *c, int j, int p)
-{
-    if (c->g[j][p]) return LF_OK;
-    return capture(c, 1 << j, p, &c->g[j][p]);
-}
-
 // Instantiate and upload every graph lf_step can launch, so that no call
 // pays for a capture or for a graph's first upload.  Runs at lf_init /
 // lf_set_state, once per context (the graphs depend only on the buffers).
+// Long graphs start from parity 0 alone: a second set from parity 1 doubled
+// this call (0.7 ms at 128^3, which a program that initialises a context per
+// gradient pays each time) to save an odd-stepped context a few launches.
 int prepare_graphs(lf_ctx *c)
 {
     if (c->graphs_ready || c->ens_member) return LF_OK;
     int rc;
-    for (int j = 0; j <= c->logK; ++j)
-        for (int p = 0; p < 2; ++p) {
-            if ((rc = ensure_graph(c, j, p))) return rc;
-            HIPCHK(hipGraphUpload(c->g[j][p], c->stream));
-        }
+    for (int j = 0; j <= c->logK + 1; ++j) {
+        hipGraphExec_t *g = j <= c->logK ? &c->g[j] : &c->g1;
+        if (!*g && (rc = capture(c, j <= c->logK ? 1 << j : 1, j <= c->logK ? 0 : 1, g))) return rc;
+        HIPCHK(hipGraphUpload(*g, c->stream));
+    }
     c->graphs_ready = 1;
     return LF_OK;
 }
@@ -556,8 +553,8 @@ int lf_destroy(lf_ctx *c)
 {
     if (!c) return LF_OK;
     for (int j = 0; j <= kMaxLogK; ++j)
-        for (int b = 0; b < 2; ++b)
-            if (c->g[j][b]) (void)hipGraphExecDestroy(c->g[j][b]);
+        if (c->g[j]) (void)hipGraphExecDestroy(c->g[j]);
+    if (c->g1) (void)hipGraphExecDestroy(c->g1);
     if (c->cap) (void)hipStreamDestroy(c->cap);
     if (c->aux) (void)hipStreamDestroy(c->aux);
     if (c->ev0) (void)hipEventDestroy(c->ev0);
@@ -623,21 +620,19 @@ int lf_step(lf_ctx *c, int64_t n)
     if (n == 0) return LF_OK;
     const int64_t n0 = n, K = (int64_t)1 << c->logK;
     int rc;
-    // every graph this call launches exists before the first event
-    if (n >= K && (rc = ensure_graph(c, c->logK, c->cur))) return rc;
-    for (int j = c->logK - 1, p = c->cur; j >= 0; --j)
-        if (n % K & ((int64_t)1 << j)) {
-            if ((rc = ensure_graph(c, j, p))) return rc;
-            if (j == 0) p ^= 1;
-        }
+    // every graph exists before the first event
+    if ((rc = prepare_graphs(c))) return rc;
     if ((rc = ensure_events(c->device, &c->ev0, &c->ev1))) return rc;
     HIPCHK(hipEventRecord(c->ev0, c->stream));
-    for (; n >= K; n -= K) HIPCHK(hipGraphLaunch(c->g[c->logK][c->cur], c->stream));
+    if (c->cur) {
+        HIPCHK(hipGraphLaunch(c->g1, c->stream));
+        c->cur = 0;
+        --n;
+    }
+    for (; n >= K; n -= K) HIPCHK(hipGraphLaunch(c->g[c->logK], c->stream));
     for (int j = c->logK - 1; j >= 0; --j)
-        if (n & ((int64_t)1 << j)) {
-            HIPCHK(hipGraphLaunch(c->g[j][c->cur], c->stream));
-            if (j == 0) c->cur ^= 1;  // an odd step count swaps the buffers
-        }
+        if (n & ((int64_t)1 << j)) HIPCHK(hipGraphLaunch(c->g[j], c->stream));
+    if (n & 1) c->cur = 1;  // an odd step count swaps the buffers
     HIPCHK(hipEventRecord(c->ev1, c->stream));
     c->timed = 1;
     c->hstep += n0;
