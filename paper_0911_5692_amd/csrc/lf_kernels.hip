@@ -482,6 +482,12 @@ __global__ void __launch_bounds__(kStage2Threads) k_rho_p_final(const double *pa
 
 // ---------------------------------------------------------------- export
 
+// A block takes kFlat x 256 sites in address order, all of its loads in flight
+// at once, and streams the results (non-temporal): FP32 to FP32 at 512^3 785
+// us a call against 925 for a grid-stride loop of plain stores (835 with one
+// site a thread, 855 with four), at 256^3 104 against 154.
+constexpr int kFlat = 2;
+
 template <typename T, typename To>
 __global__ void __launch_bounds__(256) k_get_fields(const T *__restrict__ d1, const T *__restrict__ d2,
                                                     const T *__restrict__ e1, const T *__restrict__ e2,
@@ -493,13 +499,22 @@ __global__ void __launch_bounds__(256) k_get_fields(const T *__restrict__ d1, co
     const double h = sync ? 0.5 * P->dt : 0.0;
     const double g1 = S->bg_f[0] - h * S->bg_v[0], g2 = S->bg_f[1] - h * S->bg_v[1];
     const double vb1 = S->bg_v[0], vb2 = S->bg_v[1];
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N3;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const double p = (double)e1[i], q = (double)e2[i];
-        if (f1) f1[i] = (To)(g1 + ((double)d1[i] - h * p));
-        if (f2) f2[i] = (To)(g2 + ((double)d2[i] - h * q));
-        if (v1) v1[i] = (To)(vb1 + p);
-        if (v2) v2[i] = (To)(vb2 + q);
+    const int64_t i0 = (int64_t)blockIdx.x * (256 * kFlat) + threadIdx.x;
+    T v[kFlat][4];
+#pragma unroll
+    for (int k = 0; k < kFlat; ++k) {
+        const int64_t i = i0 + 256 * k < N3 ? i0 + 256 * k : N3 - 1;
+        v[k][0] = d1[i]; v[k][1] = d2[i]; v[k][2] = e1[i]; v[k][3] = e2[i];
+    }
+#pragma unroll
+    for (int k = 0; k < kFlat; ++k) {
+        const int64_t i = i0 + 256 * k;
+        if (i >= N3) break;
+        const double p = (double)v[k][2], q = (double)v[k][3];
+        if (f1) __builtin_nontemporal_store((To)(g1 + ((double)v[k][0] - h * p)), f1 + i);
+        if (f2) __builtin_nontemporal_store((To)(g2 + ((double)v[k][1] - h * q)), f2 + i);
+        if (v1) __builtin_nontemporal_store((To)(vb1 + p), v1 + i);
+        if (v2) __builtin_nontemporal_store((To)(vb2 + q), v2 + i);
     }
 }
 
@@ -698,7 +713,7 @@ static void get_fields_t(const void *const s4[4], void *const o[4], int N, const
                          const DevScalars *S, int sync, hipStream_t st)
 {
     const int64_t N3 = (int64_t)N * N * N;
-    hipLaunchKernelGGL((k_get_fields<T, To>), dim3(grid_for(N3, 256, 65536)), dim3(256), 0, st,
+    hipLaunchKernelGGL((k_get_fields<T, To>), dim3((unsigned)((N3 + 256 * kFlat - 1) / (256 * kFlat))), dim3(256), 0, st,
                        (const T *)s4[0], (const T *)s4[1], (const T *)s4[2], (const T *)s4[3],
                        (To *)o[0], (To *)o[1], (To *)o[2], (To *)o[3], N, P, S, sync);
 }
