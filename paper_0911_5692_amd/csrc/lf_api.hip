@@ -6,6 +6,7 @@
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 #include <algorithm>
+#include <memory>
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -651,17 +652,8 @@ int lf_last_step_ms(lf_ctx *c, double *ms)
     return LF_OK;
 }
 
-int lf_energies(lf_ctx *c, lf_report *out)
+static void fill_report(const double *h, lf_report *out)
 {
-    TraceRange range_("lf_energies");
-    if (!c || !out) return fail(LF_EINVAL, "NULL argument");
-    if (!c->inited) return fail(LF_ESTATE, "lf_energies before lf_init");
-    const void *s4[4] = {c->buf[c->cur][0], c->buf[c->cur][1], c->buf[c->cur][2], c->buf[c->cur][3]};
-    launch_energy(stencil_of(&c->p), c->p.dtype, s4, c->p.N, c->P, c->S[c->cur], c->enp, kRedBlocks, c->enout, c->stream);
-    HIPCHK(hipGetLastError());
-    double h[12];
-    HIPCHK(hipMemcpyAsync(h, c->enout, sizeof h, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
     memset(out, 0, sizeof *out);
     out->step = (int64_t)h[0];
     out->a = h[1];
@@ -675,6 +667,20 @@ int lf_energies(lf_ctx *c, lf_report *out)
     out->rho = h[9];
     out->R = h[10];
     out->status = (uint32_t)h[11];
+}
+
+int lf_energies(lf_ctx *c, lf_report *out)
+{
+    TraceRange range_("lf_energies");
+    if (!c || !out) return fail(LF_EINVAL, "NULL argument");
+    if (!c->inited) return fail(LF_ESTATE, "lf_energies before lf_init");
+    const void *s4[4] = {c->buf[c->cur][0], c->buf[c->cur][1], c->buf[c->cur][2], c->buf[c->cur][3]};
+    launch_energy(stencil_of(&c->p), c->p.dtype, s4, c->p.N, c->P, c->S[c->cur], c->enp, kRedBlocks, c->enout, c->stream);
+    HIPCHK(hipGetLastError());
+    double h[kEnOut];
+    HIPCHK(hipMemcpyAsync(h, c->enout, sizeof h, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipStreamSynchronize(c->stream));
+    fill_report(h, out);
     if (out->status) return fail(LF_ENONFINITE, "non-finite value reached the volume averages");
     return LF_OK;
 }
@@ -1488,6 +1494,8 @@ struct lf_ens {
     EnsEntry *tab;       // device table (workspace)
     int4 *items;         // device work list (workspace)
     int *queue;          // device work counter of the persistent sweep (workspace)
+    double *enout;       // device energy reports (workspace)
+    int dmax;            // most blocks of a realization's energies
     int nitems, grid;
     int cur;
     hipGraphExec_t g2, g1[2];
@@ -1627,6 +1635,7 @@ int lf_ens_workspace_bytes(int R, const lf_params *per, size_t *out_bytes)
     off = align_up(off + (size_t)R * sizeof(EnsEntry));
     off = align_up(off + (size_t)nitems * sizeof(int4));
     off = align_up(off + kEnsQueueInts * sizeof(int));
+    off = align_up(off + (size_t)R * kEnOut * sizeof(double));
     *out_bytes = off;
     return LF_OK;
 }
@@ -1681,11 +1690,15 @@ int lf_ens_create(int R, const lf_params *per, void *stream, void *workspace, si
     e->items = (int4 *)(ws + off);
     off = align_up(off + (size_t)nitems * sizeof(int4));
     e->queue = (int *)(ws + off);
+    off = align_up(off + kEnsQueueInts * sizeof(int));
+    e->enout = (double *)(ws + off);
     e->nitems = nitems;
     EnsEntry *htab = new EnsEntry[R];
     int4 *hitems = new int4[nitems > 0 ? nitems : 1];
     int k = 0;
     const int target = ens_target(R, per);
+    double sites = 0.0;
+    for (int r = 0; r < R; ++r) sites += (double)per[r].N * per[r].N * per[r].N;
     for (int r = 0; r < R && rc == LF_OK; ++r) {
         lf_params q = ens_sub_params(&per[r], &per[0], target);
         rc = lf_create(&q, stream, ws + so[r], so[r + 1] - so[r], &e->sub[r]);
@@ -1708,6 +1721,11 @@ int lf_ens_create(int R, const lf_params *per, void *stream, void *workspace, si
         t.ntx = (q.N + c->sh.tile_x - 1) / c->sh.tile_x;
         t.nty = (q.N + c->sh.tile_y - 1) / c->sh.tile_y;
         t.rows = c->sh.rows;
+        // its share of the energies' blocks
+        const int share = (int)(kRedBlocks * ((double)q.N * q.N * q.N / sites));
+        ens_diag_shape(e->stencil, share < 32 ? 32 : share, &t);
+        t.enp = c->enp;
+        e->dmax = t.dgrid > e->dmax ? t.dgrid : e->dmax;
         for (int j = 0; j < c->sh.rows; ++j) hitems[k++] = make_int4(r, j, j, 0);
     }
     delete[] so;
@@ -1911,12 +1929,21 @@ int lf_ens_last_step_ms(lf_ens *e, double *ms)
 
 int lf_ens_energies(lf_ens *e, lf_report *out)
 {
+    TraceRange range_("lf_ens_energies");
     if (!e || !out) return fail(LF_EINVAL, "NULL argument");
+    int rc = ens_check_inited(e);
+    if (rc) return rc;
+    std::unique_ptr<double[]> h(new (std::nothrow) double[(size_t)e->R * kEnOut]);
+    if (!h) return fail(LF_ENOMEM, "host allocation failed");
+    launch_energy_ens(e->stencil, e->dtype, e->tab, e->R, e->dmax, e->cur, e->enout, e->stream);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipMemcpyAsync(h.get(), e->enout, (size_t)e->R * kEnOut * sizeof(double), hipMemcpyDeviceToHost,
+                          e->stream));
+    HIPCHK(hipStreamSynchronize(e->stream));
     int worst = LF_OK;
     for (int r = 0; r < e->R; ++r) {
-        int rc = lf_energies(e->sub[r], &out[r]);
-        if (rc == LF_ENONFINITE) worst = rc;
-        else if (rc) return rc;
+        fill_report(h.get() + (size_t)r * kEnOut, &out[r]);
+        if (out[r].status) worst = LF_ENONFINITE;
     }
     if (worst) return fail(worst, "non-finite value in at least one realization");
     return LF_OK;

@@ -12,6 +12,7 @@ constexpr int kMaxBeta = 6;
 constexpr int kNPart = 4;   // step reduction: sum|d+ f1|^2, sum|d+ f2|^2, sum f1^beta, sum f1^2 f2^2
 constexpr int kNMom = 10;   // input moments (see k_input_moments)
 constexpr int kNEn = 6;     // energy sums (see k_diag_march)
+constexpr int kEnOut = 12;  // numbers of an energy report (k_energy_final)
 constexpr int kStage2Threads = 256;
 constexpr int kNPow = 5;    // powers of a kept with the scalars (scale_power in lf_scale.h)
 
@@ -101,9 +102,9 @@ __device__ inline int xcd_remap(int b, int nb)
 // The same order for a grid-stride walk over nitems items: in every round
 // where the whole grid has an item, the blocks of each XCD take a contiguous
 // range of them; the last, partial round keeps the plain order.
-__device__ inline int xcd_item(int round_base, int nitems)
+__device__ inline int xcd_item(int round_base, int nitems, int bid, int nb)
 {
-    return round_base + (round_base + (int)gridDim.x <= nitems ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x);
+    return round_base + (round_base + nb <= nitems ? xcd_remap(bid, nb) : bid);
 }
 
 // One realization of an ensemble, as the batched kernels see it.
@@ -114,7 +115,10 @@ struct EnsEntry {
     const DevParams *P;
     DevScalars *S[2];       // scalars by parity
     CoefPair *Cw;           // same as C, writable (scale-factor kernel)
-    int N, zchunk, ntx, nty, rows, pad;
+    int N, zchunk, ntx, nty, rows;
+    // launch shape and partial rows of its energies
+    int dchunk, dntx, dnty, ditems, dgrid;
+    double *enp;
 };
 
 // Launch helpers (lf_kernels.hip, lf_sweep.hip).  All enqueue on `st`.
@@ -174,6 +178,11 @@ int sweep_lds27_blocks_per_cu(int dtype, int tile_x, int tile_y, int beta);
 int sweep_lds_blocks_per_cu(int stencil, int dtype, int tile_x, int tile_y, int beta);
 void launch_energy(int stencil, int dtype, const void *const st4[4], int N, const DevParams *P,
                    const DevScalars *S, double *part, int nblk, double *out_dev, hipStream_t st);
+// Energies of R realizations, kEnOut numbers each at out_dev; gmax: the largest
+// dgrid of the table (ens_diag_shape, for at most `rows` partial rows).
+void ens_diag_shape(int stencil, int rows, EnsEntry *e);
+void launch_energy_ens(int stencil, int dtype, const EnsEntry *tab, int R, int gmax, int parity, double *out_dev,
+                       hipStream_t st);
 void launch_rho_p(int stencil, int dtype, int out_dtype, const void *const s4[4], void *rho, void *pr, int N,
                   const DevParams *P, const DevScalars *S, double *part, int nblk, double *out_dev,
                   hipStream_t st);

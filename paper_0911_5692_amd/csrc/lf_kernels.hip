@@ -299,13 +299,14 @@ __device__ inline void diag_ring_cell(int c, int &lx, int &ly)
 // units): rho = sum_i K_i + G_i + V_pr, p = sum_i K_i - G_i/3 - V_pr,
 // K_i = (v_i - r (a'/a) f_i)^2/2, G_i = a^(-2s-2) grad2(f_i)/2 with grad2 the
 // stencil's gradient energy density; rho, p may be NULL.  Sums: rho, p.
+// bid, nb: this block's index among the nb that share the items.
 template <typename T, int ST, int MODE, typename To>
-__global__ void __launch_bounds__(256) k_diag_march(const T *__restrict__ d1, const T *__restrict__ d2,
-                                                    const T *__restrict__ e1, const T *__restrict__ e2, int N,
-                                                    int zchunk, int ntx, int nty, int nitems,
-                                                    const DevParams *__restrict__ P,
-                                                    const DevScalars *__restrict__ S, To *__restrict__ rho,
-                                                    To *__restrict__ pr, double *__restrict__ part)
+__device__ __forceinline__ void diag_march(const T *__restrict__ d1, const T *__restrict__ d2,
+                                           const T *__restrict__ e1, const T *__restrict__ e2, int N, int zchunk,
+                                           int ntx, int nty, int nitems, const DevParams *__restrict__ P,
+                                           const DevScalars *__restrict__ S, To *__restrict__ rho,
+                                           To *__restrict__ pr, double *__restrict__ part, const int bid,
+                                           const int nb)
 {
     constexpr int NV = MODE == 0 ? kNEn : 2;
     constexpr int NR = diag_ring<ST>();
@@ -337,11 +338,11 @@ __global__ void __launch_bounds__(256) k_diag_march(const T *__restrict__ d1, co
 #pragma unroll
     for (int i = 0; i < NV; ++i) acc[i] = 0.0;
 
-    for (int base = 0; base + (int)blockIdx.x < nitems; base += gridDim.x) {
+    for (int base = 0; base + bid < nitems; base += nb) {
         // energies: XCD-contiguous tiles share their ring rows in L2 (3% faster
         // at 512^3); rho/p, which also streams two output arrays, runs 7%
         // faster in the plain order
-        const int item = MODE == 0 ? xcd_item(base, nitems) : base + (int)blockIdx.x;
+        const int item = MODE == 0 ? xcd_item(base, nitems, bid, nb) : base + bid;
         const int tx = item % ntx, rest = item / ntx, ty = rest % nty, tz = rest / nty;
         const int x0 = tx * kDiagX, y0 = ty * DY, z0 = tz * zchunk;
         const int z1 = min(z0 + zchunk, N);
@@ -439,14 +440,37 @@ __global__ void __launch_bounds__(256) k_diag_march(const T *__restrict__ d1, co
             b0 = b1;
         }
     }
-    block_sum_store<NV>(acc, part + (size_t)blockIdx.x * NV);
+    block_sum_store<NV>(acc, part + (size_t)bid * NV);
+}
+
+template <typename T, int ST, int MODE, typename To>
+__global__ void __launch_bounds__(256) k_diag_march(const T *__restrict__ d1, const T *__restrict__ d2,
+                                                    const T *__restrict__ e1, const T *__restrict__ e2, int N,
+                                                    int zchunk, int ntx, int nty, int nitems,
+                                                    const DevParams *__restrict__ P,
+                                                    const DevScalars *__restrict__ S, To *__restrict__ rho,
+                                                    To *__restrict__ pr, double *__restrict__ part)
+{
+    diag_march<T, ST, MODE, To>(d1, d2, e1, e2, N, zchunk, ntx, nty, nitems, P, S, rho, pr, part, blockIdx.x,
+                                gridDim.x);
+}
+
+// The energies of every realization of an ensemble, block row y one of them:
+// one launch and one for the final sums instead of two and a blocking copy
+// per realization (15 of 64^3 to 160^3: 0.9 ms a call before).
+template <typename T, int ST>
+__global__ void __launch_bounds__(256) k_diag_ens(const EnsEntry *__restrict__ tab, const int parity)
+{
+    const EnsEntry &e = tab[blockIdx.y];
+    if ((int)blockIdx.x >= e.dgrid) return;
+    const T *const *b = (const T *const *)e.buf[parity];
+    diag_march<T, ST, 0, float>(b[0], b[1], b[2], b[3], e.N, e.dchunk, e.dntx, e.dnty, e.ditems, e.P, e.S[parity],
+                                nullptr, nullptr, e.enp, blockIdx.x, e.dgrid);
 }
 
 // out: step, a, a', a'/a, K1, K2, G1, G2, P, rho, R, status (as double)
-__global__ void __launch_bounds__(kStage2Threads) k_energy_final(const double *part, int nblk,
-                                                                 const DevParams *__restrict__ P,
-                                                                 const DevScalars *__restrict__ S,
-                                                                 double *out)
+__device__ inline void energy_final(const double *part, int nblk, const DevParams *__restrict__ P,
+                                    const DevScalars *__restrict__ S, double *out)
 {
     double t[kNEn];
     stage2_sum<kNEn>(part, nblk, t);
@@ -465,6 +489,21 @@ __global__ void __launch_bounds__(kStage2Threads) k_energy_final(const double *p
     out[4] = K1; out[5] = K2; out[6] = G1; out[7] = G2; out[8] = Pv; out[9] = rho;
     out[10] = (P->kappa2 > 0.0) ? R : 0.0;
     out[11] = (double)bad;
+}
+
+__global__ void __launch_bounds__(kStage2Threads) k_energy_final(const double *part, int nblk,
+                                                                 const DevParams *__restrict__ P,
+                                                                 const DevScalars *__restrict__ S,
+                                                                 double *out)
+{
+    energy_final(part, nblk, P, S, out);
+}
+
+__global__ void __launch_bounds__(kStage2Threads) k_energy_final_ens(const EnsEntry *__restrict__ tab, int parity,
+                                                                     double *out)
+{
+    const EnsEntry &e = tab[blockIdx.x];
+    energy_final(e.enp, e.dgrid, e.P, e.S[parity], out + (size_t)blockIdx.x * kEnOut);
 }
 
 // ---------------------------------------------------------------- rho and p
@@ -706,6 +745,30 @@ void launch_energy(int stencil, int dtype, const void *const s4[4], int N, const
         else g = diag_t<double, 7, 0, float>(s4, N, P, S, nullptr, nullptr, part, nblk, st);
     }
     hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(kStage2Threads), 0, st, part, g, P, S, out_dev);
+}
+
+void ens_diag_shape(int stencil, int rows, EnsEntry *e)
+{
+    const DiagShape d = diag_shape(e->N, rows, stencil == 27 ? diag_y<27>() : diag_y<7>());
+    e->dchunk = d.zchunk;
+    e->dntx = d.ntx;
+    e->dnty = d.nty;
+    e->ditems = d.items;
+    e->dgrid = d.grid;
+}
+
+void launch_energy_ens(int stencil, int dtype, const EnsEntry *tab, int R, int gmax, int parity, double *out_dev,
+                       hipStream_t st)
+{
+    const dim3 grid(gmax, R), block(256);
+    if (stencil == 27) {
+        if (dtype == 0) hipLaunchKernelGGL((k_diag_ens<float, 27>), grid, block, 0, st, tab, parity);
+        else hipLaunchKernelGGL((k_diag_ens<double, 27>), grid, block, 0, st, tab, parity);
+    } else {
+        if (dtype == 0) hipLaunchKernelGGL((k_diag_ens<float, 7>), grid, block, 0, st, tab, parity);
+        else hipLaunchKernelGGL((k_diag_ens<double, 7>), grid, block, 0, st, tab, parity);
+    }
+    hipLaunchKernelGGL(k_energy_final_ens, dim3(R), dim3(kStage2Threads), 0, st, tab, parity, out_dev);
 }
 
 template <typename T, typename To>
