@@ -318,8 +318,9 @@ int lf_autotune(const lf_params *p, void *stream, void *workspace, size_t ws_byt
  * forward map, Sec. II.B; the adjoint is this library's).  Memory: states at
  * steps 0, K, 2K, ... are checkpointed in a caller-owned workspace of
  * lf_adj_workspace_bytes bytes; the backward pass recomputes each K-step
- * segment from its checkpoint, keeps its K states in the same workspace and
- * runs the reverse steps on the exact forward states.  Two segment buffers:
+ * segment but the last (whose states the forward pass leaves there) from its
+ * checkpoint, keeps its K states in the same workspace and runs the reverse
+ * steps on the exact forward states.  Two segment buffers:
  * segment s - 1 is recomputed on a second stream of the context (default
  * priority) while the reverse steps of segment s run on its own stream.
  * Cotangents are FP64. */
