@@ -42,9 +42,9 @@
 // transform (a + i b), so odd N need nothing of their own.
 // At 512^3 (FP32 fields) one spectrum takes 1.6 ms (x pass 0.52, y 0.48, z 0.56;
 // 2.8 before: deviation 0.32, transform 1.83, shells 0.54), of which its bytes
-// (5.4 GB) take 0.9 at the rate of a plain copy; one vacuum array 2.1 ms
-// (x 1.28, y 0.22, z 0.15, y 0.22, x 0.48; 5.3 before), of which the noise's
-// arithmetic takes about 1.  Between its loads and stores a pass is bound by
+// (5.4 GB) take 0.9 at the rate of a plain copy; one vacuum array 1.75 ms
+// (x 0.93, y 0.22, z 0.15, y 0.22, x 0.48; 5.3 before), of which the noise's
+// arithmetic takes about 0.55.  Between its loads and stores a pass is bound by
 // the LDS exchanges, the twiddle loads and the FP64 arithmetic of its stages,
 // about 8 us for the 128 KB that two blocks of a CU hold, which run beside the
 // other block's memory phases in part.
@@ -87,10 +87,96 @@ __device__ inline uint4 philox4x32_10(uint4 c, uint2 k)
     return c;
 }
 
+// (m + 1) 2^-53, m the top 53 bits of the two words.
 __device__ inline double uniform53(unsigned hi, unsigned lo)
 {
-    const unsigned long long m = ((unsigned long long)hi << 21) | (lo >> 11);
-    return (double)(m + 1ull) * 0x1p-53;
+    return fma((double)hi, 0x1p-32, (double)((lo >> 11) + 1u) * 0x1p-53);
+}
+
+// The noise in FP64 is bound by its arithmetic, so its three functions are
+// written for the arguments that occur, from series and Newton steps: with the
+// math library's log, sqrt and cos (which reduce arguments of any size and
+// look for the special ones) a site took twice the instructions.  One array's
+// noise at 512^3: 0.93 -> 0.54 ms; four vacuum arrays 8.5 -> 7.1 ms.  Against 80-bit
+// arithmetic over 4 million word pairs, the ends of both uniforms among them,
+// the radius is as far off as before (rms 0.47 of 2^-53) and the noise less
+// (rms 2.8e-16 -> 1.0e-16), since the turn is no longer rounded.
+
+// A constant kept in scalar registers: the multiply-add then takes it as its
+// addend, where one in vector registers is first copied into the result.
+__device__ inline double in_sgpr(double c)
+{
+    asm("" : "+s"(c));
+    return c;
+}
+
+// log u for u = m 2^-53, 1 <= m <= 2^53: u = 2^e f with f in [sqrt(1/2), sqrt(2)),
+// t = f - 1 (exact), s = t / (2 + t), log f = 2 atanh(s) = t - s (t - s^2 Q),
+// Q = sum_k 2 s^2k / (2k + 3); since s <= 0.172 nine terms leave 1e-17.
+__device__ inline double log_unit(double u)
+{
+    constexpr double kLn2Hi = 0x1.62e42fefa3800p-1, kLn2Lo = 0x1.ef35793c76730p-45;  // e kLn2Hi is exact
+    double f = __builtin_amdgcn_frexp_mant(u);
+    int ei = __builtin_amdgcn_frexp_exp(u);
+    const bool low = f < 0.70710678118654752;
+    f = low ? f + f : f;
+    ei = low ? ei - 1 : ei;
+    const double e = (double)ei, t = f - 1.0, d = 2.0 + t;
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    double s = t * r;
+    s = fma(fma(-d, s, t), r, s);
+    const double z = s * s;
+    double q = 2.0 / 19.0;
+    q = fma(q, z, in_sgpr(2.0 / 17.0));
+    q = fma(q, z, in_sgpr(2.0 / 15.0));
+    q = fma(q, z, in_sgpr(2.0 / 13.0));
+    q = fma(q, z, in_sgpr(2.0 / 11.0));
+    q = fma(q, z, in_sgpr(2.0 / 9.0));
+    q = fma(q, z, in_sgpr(2.0 / 7.0));
+    q = fma(q, z, in_sgpr(2.0 / 5.0));
+    q = fma(q, z, in_sgpr(2.0 / 3.0));
+    const double eh = e * kLn2Hi, c = eh + t;
+    const double cl = t - (c - eh);  // c + cl = e kLn2Hi + t
+    return c - fma(s, fma(-z, q, t), -fma(e, kLn2Lo, cl));
+}
+
+// sqrt x for x = 0 or 1e-16 <= x <= 100: Newton steps from the hardware's
+// estimate of 1 / sqrt(x).
+__device__ inline double sqrt_plain(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, x), h, g);
+    return x > 0.0 ? g : 0.0;
+}
+
+// cos(2 pi u) as sin(pi y), y = 1/2 - 2 u, which is exact for the uniforms, as is
+// its remainder y - rint(y) in [-1/2, 1/2]; the series of sin(pi y) / y to y^20
+// leaves 1e-18.  (A rounded 2 pi u, as the argument of a cosine, is off by up to
+// 6e-16.)
+__device__ inline double cos_turn(double u)
+{
+    double y = fma(u, -2.0, 0.5);
+    const double k = rint(y);
+    y -= k;
+    const double z = y * y;
+    double p = 0x1.2877020d52cf0p-31;  // (-1)^k pi^(2k + 1) / (2k + 1)!
+    p = fma(p, z, in_sgpr(-0x1.8a404211f9547p-26));
+    p = fma(p, z, in_sgpr(0x1.aaec32af93359p-21));
+    p = fma(p, z, in_sgpr(-0x1.6fadb9f155744p-16));
+    p = fma(p, z, in_sgpr(0x1.e8f434d018d63p-12));
+    p = fma(p, z, in_sgpr(-0x1.e3074fde8871fp-8));
+    p = fma(p, z, in_sgpr(0x1.50783487ee782p-4));
+    p = fma(p, z, in_sgpr(-0x1.32d2cce62bd86p-1));
+    p = fma(p, z, in_sgpr(0x1.466bc6775aae2p+1));
+    p = fma(p, z, in_sgpr(-0x1.4abbce625be53p+2));
+    p = fma(p, z, in_sgpr(0x1.1a62633145c07p-53));  // pi in two parts
+    const double v = fma(y, 0x1.921fb54442d18p+1, y * p);
+    return (int)k & 1 ? -v : v;
 }
 
 // Unit normal noise of site i of array j.
@@ -98,7 +184,7 @@ __device__ inline double vacuum_noise(unsigned long long i, unsigned j, uint2 ke
 {
     const uint4 x = philox4x32_10(make_uint4((unsigned)i, (unsigned)(i >> 32), j, 0u), key);
     const double u1 = uniform53(x.x, x.y), u2 = uniform53(x.z, x.w);
-    return sqrt(-2.0 * log(u1)) * cos(2.0 * M_PI * u2);
+    return sqrt_plain(-2.0 * log_unit(u1)) * cos_turn(u2);
 }
 
 // What a mode of the noise is multiplied by: the spectrum, and the 1/N^3 of
