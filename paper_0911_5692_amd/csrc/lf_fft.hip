@@ -40,7 +40,7 @@
 // the library's transform alone reads and writes it three times besides the
 // separate passes before and after it.  Two real lines go through one complex
 // transform (a + i b), so odd N need nothing of their own.
-// At 512^3 (FP32 fields) one spectrum takes 1.6 ms (x pass 0.52, y 0.48, z 0.56;
+// At 512^3 (FP32 fields) one spectrum takes 1.55 ms (x pass 0.52, y 0.48, z 0.50;
 // 2.8 before: deviation 0.32, transform 1.83, shells 0.54), of which its bytes
 // (5.4 GB) take 0.9 at the rate of a plain copy; one vacuum array 1.75 ms
 // (x 0.93, y 0.22, z 0.15, y 0.22, x 0.48; 5.3 before), of which the noise's
@@ -305,7 +305,13 @@ int cached_plans(int N, Plans *out, std::unique_lock<std::mutex> *lock, char *ms
 
 // ---------------------------------------------------------------- spectra
 
-__device__ inline int shell_of(long long r2) { return (int)floor(sqrt((double)r2) + 0.5); }
+// The shell floor(sqrt(r2) + 1/2): m with m^2 - m < r2 <= m^2 + m, from an FP32
+// root set right by at most one.
+__device__ inline int shell_of(int r2)
+{
+    const int m = (int)(__builtin_amdgcn_sqrtf((float)r2) + 0.5f), mm = m * m;
+    return m + (r2 - mm > m) - (r2 - mm <= -m && r2 > 0);
+}
 
 // One step of the scan below: lanes that receive a value (CTRL: the DPP
 // pattern, ROWS: the rows of 16 lanes it writes) of their own shell add it.
@@ -324,7 +330,7 @@ __device__ inline void run_step(int key, double &p)
 // histogram from its last lane: one lane per shell, in a fixed order, without
 // atomics.  The lanes exchange by DPP: a scan by LDS permutes was half of the
 // z pass's time.
-__device__ inline void add_runs(int key, double p, int nbins, double *hist)
+__device__ inline void scan_runs(int key, double &p)
 {
     run_step<0x111, 0xf>(key, p);  // row_shr:1, 2, 4, 8 within 16 lanes
     run_step<0x112, 0xf>(key, p);
@@ -332,9 +338,30 @@ __device__ inline void add_runs(int key, double p, int nbins, double *hist)
     run_step<0x118, 0xf>(key, p);
     run_step<0x142, 0xa>(key, p);  // row_bcast:15 into rows 1 and 3
     run_step<0x143, 0xc>(key, p);  // row_bcast:31 into rows 2 and 3
-    const int lane = threadIdx.x & 63;
-    const int kn = __shfl_down(key, 1, 64);
-    if ((lane == 63 || kn != key) && key < nbins) hist[key] += p;
+}
+
+__device__ inline void add_runs(int key, double p, int nbins, double *hist)
+{
+    scan_runs(key, p);
+    const int kn = __builtin_amdgcn_update_dpp(-1, key, 0x130, 0xf, 0xf, false);  // wave_shl:1
+    if (kn != key && key < nbins) hist[key] += p;
+}
+
+// The same with two shells a lane, k0 <= k1: half the scans (with the shells
+// from FP32 roots, the z pass of 512^3 0.56 -> 0.50 ms).  A lane whose
+// shells differ ends the run of k0, to which the lanes before it may belong.
+// No shell is written twice: a lane's k1 only if the next lane's k0 is another.
+__device__ inline void add_runs2(int k0, double q0, int k1, double q1, int nbins, double *hist)
+{
+    const bool same = k0 == k1;
+    double p = same ? q0 + q1 : q1;
+    scan_runs(k1, p);
+    const int kn = __builtin_amdgcn_update_dpp(-1, k0, 0x130, 0xf, 0xf, false);  // wave_shl:1
+    const int kp = __builtin_amdgcn_update_dpp(-1, k1, 0x138, 0xf, 0xf, false);  // wave_shr:1
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(p), 0x138, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(p), 0x138, 0xf, 0xf, false);
+    if (!same && k0 < nbins) hist[k0] += kp == k0 ? q0 + __hiloint2double(hi, lo) : q0;
+    if (kn != k1 && k1 < nbins) hist[k1] += p;
 }
 
 // One block of nw = blockDim.x / 64 waves per kz plane; wave w walks the rows
@@ -349,17 +376,17 @@ __global__ void __launch_bounds__(512) k_spectrum_bins(const double2 *__restrict
     __syncthreads();
     const int NH = N / 2 + 1, kz = blockIdx.x;
     if (kz == 0 && t == 0) *F0 = W[0].x;
-    const long long nz = kz <= N / 2 ? kz : kz - N;
+    const int nz = kz <= N / 2 ? kz : kz - N;
     for (int ky = wv; ky < N; ky += nw) {
-        const long long ny = ky <= N / 2 ? ky : ky - N;
-        const long long r2 = ny * ny + nz * nz;
+        const int ny = ky <= N / 2 ? ky : ky - N;
+        const int r2 = ny * ny + nz * nz;
         const double2 *row = W + ((size_t)kz * N + ky) * NH;
         for (int x0 = 0; x0 < NH; x0 += 64) {
             const int kx = x0 + lane;
             int key = 0x7fffffff;
             double p = 0.0;
             if (kx < NH) {
-                key = shell_of(r2 + (long long)kx * kx);
+                key = shell_of(r2 + kx * kx);
                 const double w = (kx == 0 || 2 * kx == N) ? 1.0 : 2.0;
                 const double2 v = row[kx];
                 p = w * (v.x * v.x + v.y * v.y);
@@ -725,7 +752,7 @@ __global__ void __launch_bounds__(NT, fft_waves(NT, EXACT)) k_fft_z_bins(const d
     const int N = pl.N, t = threadIdx.x, lane = t & 63, wv = t >> 6;
     double *hist = (double *)(s + (size_t)N * B);  // [wave][nbins]
     for (int b = t; b < nh * nbins; b += NT) hist[b] = 0.0;
-    const int H = N / 2 + 1, c = t % B;
+    const int HP = (N + 1) / 2, c = t % B;  // kz of which kz and -kz both occur, and 0
     const long long plane = (long long)N * NS;
     double2 v[kFftPts];
     auto load = [&](int item) {
@@ -751,26 +778,46 @@ __global__ void __launch_bounds__(NT, fft_waves(NT, EXACT)) k_fft_z_bins(const d
         if (item + (int)gridDim.x < N * ntile) load(item + gridDim.x);
         if (item == 0 && t == 0) *F0 = s[fft_slot<B>(0, 0)].x;
         if (wv < nh) {
-            const long long ny = ky <= N / 2 ? ky : ky - N;
+            const int ny = ky <= N / 2 ? ky : ky - N;
+            double *hp = hist + (size_t)wv * nbins;
             for (int cc = wv; cc < B && kx0 + cc < nk; cc += nh) {
-                const long long kx = kx0 + cc, r2 = kx * kx + ny * ny;
+                const int kx = kx0 + cc, r2 = kx * kx + ny * ny;
                 const double w = (kx == 0 || 2 * kx == N) ? 1.0 : 2.0;
-                for (int z0 = 0; z0 < H; z0 += 64) {
-                    const int kz = z0 + lane;
-                    int key = 0x7fffffff;
-                    double q = 0.0;
-                    if (kz < H) {
-                        key = shell_of(r2 + (long long)kz * kz);
-                        const double2 a = s[fft_slot<B>(kz, cc)];
-                        q = a.x * a.x + a.y * a.y;
-                        if (kz > 0 && 2 * kz != N) {
-                            const double2 b = s[fft_slot<B>(N - kz, cc)];
-                            q += b.x * b.x + b.y * b.y;
+                auto power = [&](int kz) {
+                    const double2 a = s[fft_slot<B>(kz, cc)], b = s[fft_slot<B>(kz ? N - kz : 0, cc)];
+                    const double q = a.x * a.x + a.y * a.y;
+                    return w * (kz ? q + (b.x * b.x + b.y * b.y) : q);
+                };
+                for (int z0 = 0; z0 < HP; z0 += 128) {
+                    const int kz = z0 + 2 * lane;
+                    int k0 = 0x7fffffff, k1 = 0x7fffffff;
+                    double q0 = 0.0, q1 = 0.0;
+                    if (kz < HP) {
+                        // eight lanes the even one first, eight the odd one: all banks
+                        const bool odd = (lane & 8) && kz + 1 < HP;
+                        k0 = shell_of(r2 + kz * kz);
+                        q0 = power(kz + odd);
+                        if (kz + 1 < HP) {
+                            k1 = shell_of(r2 + (kz + 1) * (kz + 1));
+                            q1 = power(kz + !odd);
                         }
-                        q *= w;
+                        const double x = odd ? q1 : q0;
+                        q1 = odd ? q0 : q1;
+                        q0 = x;
                     }
-                    add_runs(key, q, nbins, hist + (size_t)wv * nbins);
+                    add_runs2(k0, q0, k1, q1, nbins, hp);
                 }
+            }
+            if (wv == 0 && 2 * HP == N) {  // N even: kz = N/2 of the tile's columns
+                const int kx = kx0 + lane;
+                int key = 0x7fffffff;
+                double q = 0.0;
+                if (lane < B && kx < nk) {
+                    key = shell_of(kx * kx + ny * ny + HP * HP);
+                    const double2 a = s[fft_slot<B>(HP, lane)];
+                    q = ((kx == 0 || 2 * kx == N) ? 1.0 : 2.0) * (a.x * a.x + a.y * a.y);
+                }
+                add_runs(key, q, nbins, hp);
             }
         }
         __syncthreads();
@@ -808,7 +855,7 @@ namespace {
 // no faster, through hipFFT.  Both ways measured (spectra of four fields; the
 // whole vacuum state; us):
 //   powers of two from 128: 128^3 667 -> 518 and 497 -> 339, 256^3 1775 -> 1168
-//     and 2505 -> 1223, 512^3 11090 -> 6630 and 22210 -> 8520;
+//     and 2505 -> 1223, 512^3 11090 -> 6400 and 22210 -> 7070;
 //   factors of 3, 5 and 7, whose butterflies leave one block per CU: vacuum
 //     100^3 388 -> 316, 210^3 1831 -> 1472, 400^3 13382 -> 7706; but spectra
 //     200^3 980 -> 1138, 400^3 6965 -> 7269;
