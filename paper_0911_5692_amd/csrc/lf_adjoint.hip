@@ -24,6 +24,7 @@
 // deviations from the FP64 background and are turned back into full fields
 // f = f_bar + d in FP64 on the fly.
 #include "lf_internal.h"
+#include "lf_scale.h"
 
 #include <math.h>
 
@@ -38,10 +39,7 @@ __device__ inline void bsum(double (&v)[NV], double *out)
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        double x = v[i];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-        v[i] = x;
+        v[i] = wave_sum(v[i]);
     }
     if (lane == 0) {
 #pragma unroll

@@ -23,10 +23,7 @@ __device__ inline void block_sum_store(double (&v)[NV], double *out)
     const int lane = t & 63, wave = t >> 6, nw = (nthreads + 63) >> 6;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        double x = v[i];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-        v[i] = x;
+        v[i] = wave_sum(v[i]);
     }
     if (lane == 0) {
 #pragma unroll

@@ -428,10 +428,7 @@ __device__ __forceinline__ void sweep_tile27(const T *__restrict__ d1, const T *
     __shared__ double red[4][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        double x = v[i];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-        v[i] = x;
+        v[i] = wave_sum(v[i]);
     }
     if (lane == 0) {
 #pragma unroll

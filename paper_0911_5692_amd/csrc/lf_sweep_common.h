@@ -110,8 +110,7 @@ __device__ inline void step_totals(const StepSource &q, const ScaleIn &in, doubl
         double x = 0.0;
 #pragma unroll
         for (int k = 0; k < kRows; ++k) x += row[k][i];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+        x = wave_sum(x);
         if (lane == 0) sm[i][w] = x;
     }
     __syncthreads();
@@ -146,9 +145,9 @@ __device__ inline void step_extra_block(const StepSource &q)
 // when a scale-factor kernel ran.  A kernel of its own for this chain of
 // dependent FP64 operations on one block takes 5 to 6 us between two sweeps
 // in which the device does nothing else; in every block of the sweep it
-// takes about 3.  Step times, two kernels against one: 32^3 FP64 10.8 ->
-// 8.8 us, 128^3 FP32 25.6 -> 23.8, 256^3 114.3 -> 110.9, 512^3 792 -> 789
-// (7 points).  `first`: this block writes the results.
+// takes about 2.  Step times, two kernels against one, with wave sums by LDS
+// permutes on both sides: 32^3 FP64 10.8 -> 8.8 us, 128^3 FP32 25.6 -> 23.8,
+// 256^3 114.3 -> 110.9, 512^3 792 -> 789 (7 points).  `first`: this block writes the results.
 struct CoefsOfStep {
     const StepSource &q;
     const bool first;
