@@ -1737,8 +1737,6 @@ int lf_ens_create(int R, const lf_params *per, void *stream, void *workspace, si
     int4 *hitems = new int4[nitems > 0 ? nitems : 1];
     int k = 0;
     const int target = ens_target(R, per);
-    double sites = 0.0;
-    for (int r = 0; r < R; ++r) sites += (double)per[r].N * per[r].N * per[r].N;
     for (int r = 0; r < R && rc == LF_OK; ++r) {
         lf_params q = ens_sub_params(&per[r], &per[0], target);
         rc = lf_create(&q, stream, ws + so[r], so[r + 1] - so[r], &e->sub[r]);
@@ -1761,9 +1759,8 @@ int lf_ens_create(int R, const lf_params *per, void *stream, void *workspace, si
         t.ntx = (q.N + c->sh.tile_x - 1) / c->sh.tile_x;
         t.nty = (q.N + c->sh.tile_y - 1) / c->sh.tile_y;
         t.rows = c->sh.rows;
-        // its share of the energies' blocks
-        const int share = (int)(kRedBlocks * ((double)q.N * q.N * q.N / sites));
-        ens_diag_shape(e->stencil, share < 32 ? 32 : share, &t);
+        // the energies in a lone lattice's blocks and rows, so in its bits too
+        ens_diag_shape(e->stencil, kRedBlocks, &t);
         t.enp = c->enp;
         e->dmax = t.dgrid > e->dmax ? t.dgrid : e->dmax;
         for (int j = 0; j < c->sh.rows; ++j) hitems[k++] = make_int4(r, j, j, 0);

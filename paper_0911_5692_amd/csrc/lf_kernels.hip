@@ -454,7 +454,8 @@ __global__ void __launch_bounds__(256) k_diag_march(const T *__restrict__ d1, co
 
 // The energies of every realization of an ensemble, block row y one of them:
 // one launch and one for the final sums instead of two and a blocking copy
-// per realization (15 of 64^3 to 160^3: 0.9 ms a call before).
+// per realization (15 of 64^3 to 160^3: 0.9 ms a call before).  Blocks and rows
+// are those of a lone lattice's energies, so the bits are too.
 template <typename T, int ST>
 __global__ void __launch_bounds__(256) k_diag_ens(const EnsEntry *__restrict__ tab, const int parity)
 {
@@ -757,13 +758,16 @@ void ens_diag_shape(int stencil, int rows, EnsEntry *e)
 void launch_energy_ens(int stencil, int dtype, const EnsEntry *tab, int R, int gmax, int parity, double *out_dev,
                        hipStream_t st)
 {
-    const dim3 grid(gmax, R), block(256);
-    if (stencil == 27) {
-        if (dtype == 0) hipLaunchKernelGGL((k_diag_ens<float, 27>), grid, block, 0, st, tab, parity);
-        else hipLaunchKernelGGL((k_diag_ens<double, 27>), grid, block, 0, st, tab, parity);
-    } else {
-        if (dtype == 0) hipLaunchKernelGGL((k_diag_ens<float, 7>), grid, block, 0, st, tab, parity);
-        else hipLaunchKernelGGL((k_diag_ens<double, 7>), grid, block, 0, st, tab, parity);
+    const dim3 block(256);
+    for (int r = 0; r < R; r += 65535) {  // the most block rows of a launch
+        const dim3 grid(gmax, R - r < 65535 ? R - r : 65535);
+        if (stencil == 27) {
+            if (dtype == 0) hipLaunchKernelGGL((k_diag_ens<float, 27>), grid, block, 0, st, tab + r, parity);
+            else hipLaunchKernelGGL((k_diag_ens<double, 27>), grid, block, 0, st, tab + r, parity);
+        } else {
+            if (dtype == 0) hipLaunchKernelGGL((k_diag_ens<float, 7>), grid, block, 0, st, tab + r, parity);
+            else hipLaunchKernelGGL((k_diag_ens<double, 7>), grid, block, 0, st, tab + r, parity);
+        }
     }
     hipLaunchKernelGGL(k_energy_final_ens, dim3(R), dim3(kStage2Threads), 0, st, tab, parity, out_dev);
 }
