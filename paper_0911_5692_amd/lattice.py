@@ -231,7 +231,9 @@ class Lattice:
         return ms.value
 
     def time_kernels(self, n: int):
-        """Average ms per kernel over n eager steps: (a-update, sweep, reduce)."""
+        """Average ms per kernel over n eager steps: (a-update, sweep, reduce).
+        Where the sweep updates the scale factor itself, the first is the time
+        between two events with no kernel between them."""
         ms = (ctypes.c_double * 3)()
         check(lib().lf_time_kernels(self._ctx, int(n), ms, 3))
         return tuple(ms)

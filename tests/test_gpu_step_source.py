@@ -33,3 +33,27 @@ def test_update_in_the_sweep(N, tx, ty, zc, rows, stencil):
         e = lat.energies()
         assert abs(e["ad"] - st.ad) <= 1e-12 * abs(st.ad)
     lat.close()
+
+
+@pytest.mark.parametrize("N", [271, 272])
+def test_27_points_with_and_without_the_update(N):
+    """The largest lattice whose FP32 27-point sweep in 128 x 8 tiles updates
+    the scale factor, and the smallest whose sweep reads it, against 64 x 8
+    tiles, which always update it."""
+    m = {**W.CFG3.resized(N).model(), "stencil": 27}
+    g = torch.Generator(device="cuda").manual_seed(N)
+    ic = [b + 1e-3 * torch.randn((N, N, N), dtype=torch.float64, device="cuda", generator=g)
+          for b in (1.0, 0.0, -0.7, 0.0)]
+    res = []
+    for tx in (128, 64):
+        lat = Lattice(**m, dtype=torch.float32, tile_x=tx, tile_y=8, zchunk=128)
+        lat.init_physical(*ic)
+        lat.step(5)
+        res.append((lat.fields(), lat.energies()))
+        lat.close()
+    (fa, ea), (fb, eb) = res
+    # the same site arithmetic; the sums in another order move a by about 1e-16
+    # a step, which may turn the rounding of a coefficient
+    for a, b in zip(fa, fb):
+        assert float((a - b).abs().max()) <= 1e-6 * float(b.abs().max())
+    assert abs(ea["ad"] - eb["ad"]) <= 1e-12 * abs(eb["ad"])
