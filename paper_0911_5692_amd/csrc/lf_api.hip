@@ -163,12 +163,26 @@ int auto_zchunk(const lf_params *p, int tile_x, int tile_y, int nz)
     return best_zchunk(p, tile_x, tile_y, nz, &cost);
 }
 
+// The 7-point update of a site rounds in one of two ways with beta 4 and 5
+// (Coefs::force): one in tiles of one site a thread, the other in wider tiles.
+// In FP32 the two differ by some 1e-8 of a gradient, so the choice among tiles
+// stays within one kind for a given N: one site a thread below 96, wider from there.
+// Step times with and without this rule, beta 4: 33^3 7.6 us both, 48^3 8.1 and 8.2,
+// 64^3 8.8 and 8.6, 80^3 11.8 and 11.7, 95^3 15.4 and 13.3.
+constexpr int kOneSiteBelow = 96;
+
+bool same_rounding(const lf_params *p, const TileCost &t)
+{
+    if (p->dtype != LF_F32 || stencil_of(p) != 7 || (p->beta != 4 && p->beta != 5)) return true;
+    return (t.tx * t.ty == 256) == (p->N < kOneSiteBelow);
+}
+
 void auto_shape(const lf_params *p, int *tile_x, int *tile_y, int *zchunk)
 {
     const ShapeModel &m = shape_model(p->dtype, stencil_of(p));
     double best = 1e300;
     for (const TileCost &t : m.tile) {
-        if (!t.tx) continue;
+        if (!t.tx || !same_rounding(p, t)) continue;
         double c;
         const int z = best_zchunk(p, t.tx, t.ty, p->N, &c);
         if (c * t.plane < best) {
