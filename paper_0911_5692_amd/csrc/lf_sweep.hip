@@ -13,7 +13,8 @@
 //   G a^p2 [f1 f2^2 - g1 g2^2] = C2 [d1 (g2+d2)^2 + g1 d2 (2 g2 + d2)]
 //   G a^p2 [f1^2 f2 - g1^2 g2] = C2 [d1 (2 g1 + d1)(g2 + d2) + g1^2 d2]
 //
-// Two implementations of the same per-site arithmetic (identical rounding):
+// Two implementations of the same per-site arithmetic (Coefs::force; for
+// which beta and tiles the roundings are identical: horner_rounded):
 //
 // k_sweep_lds — the production kernel.  A block of 256 threads owns a
 //   TX (x, 64 or 128) x TY (y) column tile and marches a chunk of z planes.
@@ -82,12 +83,12 @@ __global__ void __launch_bounds__(256) k_sweep_plain(const T *__restrict__ d1, c
         lb = lap_raw<27, T>([&](int dx, int dy, int dz) { return d2[idx(dx, dy, dz)]; }, b);
     }
     T ia, ib;
-    c.force(a, b, la, lb, ia, ib);
+    c.template force<horner_rounded(NH, NH > 3)>(a, b, la, lb, ia, ib);
     const T ea = e1[i] + ia, eb = e2[i] + ib;
     e1n[i] = ea;
     e2n[i] = eb;
-    d1n[i] = a + c.dt * ea;
-    d2n[i] = b + c.dt * eb;
+    d1n[i] = fma(c.dt, ea, a);
+    d2n[i] = fma(c.dt, eb, b);
 }
 
 // Single lattice: one block per (tile, z-chunk), XCD-aware tile order.

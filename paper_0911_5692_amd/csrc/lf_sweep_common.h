@@ -30,22 +30,27 @@ struct Coefs {
     // Velocity increments of both fields at one site from the raw stencil
     // sums (s6a, s6b: the integer-weighted neighbour sum including the centre
     // term; Cl carries 1/dx^2 and the stencil weight) and the deviations
-    // a = d1, b = d2.
+    // a = d1, b = d2.  Every multiply-add is an explicit fma, so that each
+    // inlined copy rounds alike: a ring site then equals, to the bit, the site
+    // that the neighbouring tile stores.  HORNER_ROUNDED: which of the two
+    // products of dv1 = hor a + C2 q is rounded before they are added.
+    template <bool HORNER_ROUNDED>
     __device__ inline void force(T a, T b, T s6a, T s6b, T &inc_a, T &inc_b) const
     {
+#pragma clang fp contract(off)
         T hor = h[NH - 1];
 #pragma unroll
-        for (int j = NH - 2; j >= 0; --j) hor = hor * a + h[j];
+        for (int j = NH - 2; j >= 0; --j) hor = fma(hor, a, h[j]);
         const T t2 = g2 + b;
-        const T dv1 = hor * a + C2 * (a * t2 * t2 + g1 * b * (two_g2 + b));
-        const T dv2 = C2 * (a * (two_g1 + a) * t2 + g1sq * b);
-        inc_a = (Cl * s6a + Cf * a) - dv1;
-        inc_b = (Cl * s6b + Cf * b) - dv2;
+        const T q = fma(g1 * b, two_g2 + b, (a * t2) * t2);
+        const T dv1 = HORNER_ROUNDED ? fma(q, C2, hor * a) : fma(hor, a, C2 * q);
+        const T w = fma(g1sq, b, (a * (two_g1 + a)) * t2);
+        inc_a = fma(Cf, a, Cl * s6a) - dv1;
+        inc_b = fma(-C2, w, fma(Cf, b, Cl * s6b));
     }
-    // The same increments with every multiply-add an explicit fma, so that
-    // each inlined copy rounds alike whatever the compiler would contract
-    // (the 27-point sweep computes a site in several copies of its loop and,
-    // redundantly, as another tile's ring site).
+    // The same increments as the 27-point sweep rounds them (it too computes a
+    // site in several copies of its loop and, redundantly, as another tile's
+    // ring site).
     __device__ inline void force_fma(T a, T b, T s6a, T s6b, T &inc_a, T &inc_b) const
     {
         T hor = h[NH - 1];
@@ -59,10 +64,15 @@ struct Coefs {
     }
 };
 
+// Coefs::force of the 7-point sweeps: one rounding for beta 2, 3 and 6, and for
+// beta 4 and 5 one in tiles of one site a thread and the other in wider ones.
+// These are the roundings that stored results were made with.
+constexpr bool horner_rounded(int nh, bool wide) { return nh == 5 || (nh >= 3 && wide); }
+
 template <typename T>
 __device__ inline T six_sum(T xm, T xp, T ym, T yp, T zm, T zp, T c)
 {
-    return (((xm + xp) + (ym + yp)) + (zm + zp)) - T(6) * c;
+    return fma(T(-6), c, ((xm + xp) + (ym + yp)) + (zm + zp));
 }
 
 template <int NH>

@@ -36,6 +36,7 @@ __device__ __forceinline__ void sweep_tile(const T *__restrict__ d1, const T *__
     constexpr int NRING = TX + 1 + TY;          // row y0-1 (TX), corner, column x0-1 (TY)
     constexpr int NHALO = 2 * (TX + 1) + 2 * (TY + 1);
     static_assert(256 % TX == 0 && TY % RPR == 0 && NRING <= 256 && NHALO <= 512, "tile shape");
+    constexpr bool HR = horner_rounded(NH, KI > 1);
     // double-buffered: plane z is read from buffer (z - z0 + 1) & 1 while
     // plane z+1 is staged into the other one; one barrier per plane
     __shared__ T sd[2][2][LH * LW];
@@ -210,9 +211,9 @@ __device__ __forceinline__ void sweep_tile(const T *__restrict__ d1, const T *__
             const T sa = six_sum(s0[l - 1], s0[l + 1], s0[l - LW], s0[l + LW], qm1[k], qp1[k], qc1[k]);
             const T sb = six_sum(s1[l - 1], s1[l + 1], s1[l - LW], s1[l + LW], qm2[k], qp2[k], qc2[k]);
             T ia, ib;
-            c.force(qc1[k], qc2[k], sa, sb, ia, ib);
+            c.template force<HR>(qc1[k], qc2[k], sa, sb, ia, ib);
             const T ea = ev1[k] + ia, eb = ev2[k] + ib;
-            const T na = qc1[k] + c.dt * ea, nb = qc2[k] + c.dt * eb;
+            const T na = fma(c.dt, ea, qc1[k]), nb = fma(c.dt, eb, qc2[k]);
             pe1[k] = ea; pe2[k] = eb; pd1[k] = na; pd2[k] = nb;
             n0[lsn[k]] = na;
             n1[lsn[k]] = nb;
@@ -226,9 +227,9 @@ __device__ __forceinline__ void sweep_tile(const T *__restrict__ d1, const T *__
             const T sa = six_sum(s0[l - 1], s0[l + 1], s0[l - LW], s0[l + LW], rqm1, rqp1, rqc1);
             const T sb = six_sum(s1[l - 1], s1[l + 1], s1[l - LW], s1[l + LW], rqm2, rqp2, rqc2);
             T ia, ib;
-            c.force(rqc1, rqc2, sa, sb, ia, ib);
-            n0[rlsn] = rqc1 + c.dt * (rev1 + ia);
-            n1[rlsn] = rqc2 + c.dt * (rev2 + ib);
+            c.template force<HR>(rqc1, rqc2, sa, sb, ia, ib);
+            n0[rlsn] = fma(c.dt, rev1 + ia, rqc1);
+            n1[rlsn] = fma(c.dt, rev2 + ib, rqc2);
         }
         // stage plane z+1 into the other buffer (data loaded earlier)
         if (more) {
