@@ -325,22 +325,8 @@ struct lf_ctx {
 
 namespace {
 
-// Above so many sites the FP32 27-point sweep in tiles of k27LeanTile leaves the
-// scale factor to a kernel of its own: that takes 6 us a step, the registers
-// it would spill 3 to 5% of the sweep.  In the sweep against separate, 20 steps
-// and the export: 512^3 20.0 -> 19.4 ms, 400^3 11.65 -> 11.1; the other way round
-// at 256^3, 50 steps and the export: 6.55 against 6.65.
-constexpr long long k27LeanSites = 20000000;
-
 // Whether the sweep forms the scale-factor update in its own blocks.
-bool step_fused(const lf_ctx *c)
-{
-    const long long sites = (long long)c->p.N * c->p.N * c->p.N;
-    if (stencil_of(&c->p) == 27 && c->p.dtype == LF_F32 && c->sh.tile_x * c->sh.tile_y == k27LeanTile &&
-        sites > k27LeanSites)
-        return false;
-    return c->sh.tile_y != 1 && c->sh.rows <= kFusedRows;
-}
+bool step_fused(const lf_ctx *c) { return c->sh.tile_y != 1 && c->sh.rows <= kFusedRows; }
 
 // One leapfrog step: FP64 scale-factor update from the pending partial sums
 // and scalars of parity p, and the fused kick-drift sweep from the arrays

@@ -68,11 +68,6 @@ struct StepSource {
 // pass is the cheaper one.
 constexpr int kFusedRows = 1024;
 
-// The FP32 27-point sweep in tiles of this many sites (four a thread) fills the
-// register file, and forming the step's coefficients in it spills eight
-// registers; it also exists without.
-constexpr int k27LeanTile = 1024;
-
 // Per-step coefficients of the fused kick-drift, written by the scale-factor
 // kernel in both precisions (the sweep reads its own).
 template <typename T>

@@ -47,30 +47,24 @@
 
 namespace lf {
 
-// STEP: the block forms the step's coefficients unless a scale-factor kernel
-// did (StepSource); without, it only reads them.
-template <typename T, int NH, int TX, int TY, bool STEP>
+template <typename T, int NH, int TX, int TY>
 __global__ void __launch_bounds__(256, LF_SWEEP27_WAVES(T)) k_sweep_lds27(
     const T *__restrict__ d1, const T *__restrict__ d2, const T *__restrict__ e1, const T *__restrict__ e2,
     T *__restrict__ d1n, T *__restrict__ d2n, T *__restrict__ e1n, T *__restrict__ e2n, const int N,
     const int zchunk, const int ntx, const int nty, const StepSource src, double *__restrict__ part)
 {
     const int ntiles = gridDim.x - src.extra;
-    if (STEP && (int)blockIdx.x == ntiles) {
+    if ((int)blockIdx.x == ntiles) {
         step_extra_block(src);
         return;
     }
-    const auto coefs = [&] {
-        if constexpr (STEP) return [&](int tile) { return CoefsOfStep(src, !src.extra && tile == 0); };
-        else return [&](int) { return CoefsFrom{src.C}; };
-    }();
     const int tile = xcd_remap(blockIdx.x, ntiles);
     const int tx = tile % ntx, b = tile / ntx;
     const int ty = b % nty;
     const int tz = b / nty;
     const int z0 = tz * zchunk;
     sweep_tile27<T, NH, TX, TY, false>(d1, d2, e1, e2, d1n, d2n, e1n, e2n, N, ZPlanes<T>{}, tx * TX, ty * TY,
-                                       z0, min(z0 + zchunk, N), coefs(tile), part + (size_t)tile * kNPart);
+                                       z0, min(z0 + zchunk, N), CoefsOfStep(src, !src.extra && tile == 0), part + (size_t)tile * kNPart);
 }
 
 template <typename T, int NH, int TX, int TY>
@@ -104,18 +98,10 @@ void lds27_t(int tile_x, int tile_y, int beta, const void *const in[4], void *co
         with_nh(beta, [&](auto nh) {
             constexpr int NH = decltype(nh)::value;
             const int ntx = (N + TX - 1) / TX, nty = (N + TY - 1) / TY, nzc = (N + zchunk - 1) / zchunk;
-            auto launch = [&](auto *kernel) {
-                hipLaunchKernelGGL(kernel, dim3(ntx * nty * nzc + src.extra), dim3(256), 0, st, (const T *)in[0],
-                                   (const T *)in[1], (const T *)in[2], (const T *)in[3], (T *)out[0], (T *)out[1],
-                                   (T *)out[2], (T *)out[3], N, zchunk, ntx, nty, src, part);
-            };
-            if constexpr (sizeof(T) == 4 && TX * TY == k27LeanTile) {
-                if (!src.part) {
-                    launch(k_sweep_lds27<T, NH, TX, TY, false>);
-                    return;
-                }
-            }
-            launch(k_sweep_lds27<T, NH, TX, TY, true>);
+            hipLaunchKernelGGL((k_sweep_lds27<T, NH, TX, TY>), dim3(ntx * nty * nzc + src.extra), dim3(256), 0, st,
+                               (const T *)in[0], (const T *)in[1], (const T *)in[2], (const T *)in[3],
+                               (T *)out[0], (T *)out[1], (T *)out[2], (T *)out[3], N, zchunk, ntx, nty, src,
+                               part);
         });
     });
 }
@@ -143,7 +129,7 @@ int occ27_t(int tile_x, int tile_y, int beta)
         constexpr int TX = decltype(tx)::value, TY = decltype(ty)::value;
         with_nh(beta, [&](auto nh) {
             constexpr int NH = decltype(nh)::value;
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep_lds27<T, NH, TX, TY, true>, 256, 0);
+            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep_lds27<T, NH, TX, TY>, 256, 0);
         });
     });
     return e == hipSuccess ? nb : 0;

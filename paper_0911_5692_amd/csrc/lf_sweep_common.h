@@ -20,7 +20,8 @@ template <typename T, int NH>
 struct Coefs {
     T Cl, Cf, dt, C2, g1, g2, two_g1, two_g2, g1sq;
     T h[NH];
-    __device__ inline void load(const Coef<T> &c)
+    template <typename C>
+    __device__ inline void load(const C &c)
     {
         Cl = c.Cl; Cf = c.Cf; dt = c.dt; C2 = c.C2; g1 = c.g1; g2 = c.g2;
         two_g1 = c.two_g1; two_g2 = c.two_g2; g1sq = c.g1sq;
@@ -157,7 +158,12 @@ __device__ inline void step_extra_block(const StepSource &q)
 // in which the device does nothing else; in every block of the sweep it
 // takes about 2.  Step times, two kernels against one, with wave sums by LDS
 // permutes on both sides: 32^3 FP64 10.8 -> 8.8 us, 128^3 FP32 25.6 -> 23.8,
-// 256^3 114.3 -> 110.9, 512^3 792 -> 789 (7 points).  `first`: this block writes the results.
+// 256^3 114.3 -> 110.9, 512^3 792 -> 789 (7 points).  The coefficients stay in
+// scalar registers: in vector ones (as they were without the measures taken in
+// get() and uniform()) the sweeps that fill the register file spilled inside their
+// loops.  FP64 32x16 tiles at 200^3 315 -> 135 us, FP32 64x16 at 256^3 177 -> 126,
+// FP64 27 points at 256^3 246 -> 235, FP32 27 points at 160^3 46.2 -> 43.3.
+// `first`: this block writes the results.
 struct CoefsOfStep {
     const StepSource &q;
     const bool first;
@@ -166,7 +172,13 @@ struct CoefsOfStep {
     __device__ inline void get(Coefs<T, NH> &c, double &g1n, double &g2n) const
     {
         if (!q.part) {
-            CoefsFrom{q.C}.template get<T, NH>(c, g1n, g2n);
+            // in scalar loads: from vector ones, the values of both branches
+            // would live in vector registers
+            InConst<CoefPair> *C = in_const(q.C);
+            if constexpr (sizeof(T) == 4) c.load(C->f);
+            else c.load(C->d);
+            g1n = C->g1n;
+            g2n = C->g2n;
             return;
         }
         const ScaleIn in(q.P, q.S);
@@ -175,8 +187,8 @@ struct CoefsOfStep {
         ScaleStep o;
         scale_step(tot, in, NH + 1, o);
         const double g1 = in.g1, g2 = in.g2;
-        c.Cl = uniform((T)o.Cl); c.Cf = uniform((T)o.Cf); c.dt = (T)in.dt; c.C2 = uniform((T)o.C2);
-        c.g1 = (T)g1; c.g2 = (T)g2;
+        c.Cl = uniform((T)o.Cl); c.Cf = uniform((T)o.Cf); c.dt = uniform((T)in.dt); c.C2 = uniform((T)o.C2);
+        c.g1 = uniform((T)g1); c.g2 = uniform((T)g2);
         c.two_g1 = uniform((T)(2.0 * g1)); c.two_g2 = uniform((T)(2.0 * g2)); c.g1sq = uniform((T)(g1 * g1));
 #pragma unroll
         for (int j = 0; j < NH; ++j) c.h[j] = uniform((T)scale_h(o.ch, NH + 1, j + 1, g1));
