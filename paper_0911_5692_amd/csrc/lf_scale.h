@@ -12,21 +12,15 @@
 
 namespace lf {
 
-// Uniform values into scalar registers.  Arithmetic on floating-point values is
-// vector arithmetic, also of uniform ones, and the compiler drops a lane read of
-// what it knows to be uniform, or moves it to where the value came from, and keeps
-// the result in a vector register; the empty asm hides where the value came from.
+// Uniform values from vector into scalar registers.
 __device__ inline float uniform(float x)
 {
-    int v = __float_as_int(x);
-    asm("" : "+v"(v));
-    return __int_as_float(__builtin_amdgcn_readfirstlane(v));
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
 __device__ inline double uniform(double x)
 {
-    int hi = __double2hiint(x), lo = __double2loint(x);
-    asm("" : "+v"(hi), "+v"(lo));
-    return __hiloint2double(__builtin_amdgcn_readfirstlane(hi), __builtin_amdgcn_readfirstlane(lo));
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(x)),
+                            __builtin_amdgcn_readfirstlane(__double2loint(x)));
 }
 
 // The sum over a wave, in every lane: lanes 32 apart are added first, then 16,

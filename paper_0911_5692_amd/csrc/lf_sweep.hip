@@ -110,7 +110,8 @@ __global__ void __launch_bounds__(256, LF_SWEEP_MIN_WAVES) k_sweep_lds(
     const int tz = b / nty;
     const int z0 = tz * zchunk;
     sweep_tile<T, NH, TX, TY, LF_SWEEP_PREFETCH, false>(d1, d2, e1, e2, d1n, d2n, e1n, e2n, N, ZPlanes<T>{},
-                                                        tx * TX, ty * TY, z0, min(z0 + zchunk, N), CoefsOfStep(src, !src.extra && tile == 0),
+                                                        tx * TX, ty * TY, z0, min(z0 + zchunk, N),
+                                                        StepCoefs<T, TX, TY>(src, !src.extra && tile == 0),
                                                         part + (size_t)tile * kNPart);
 }
 

@@ -64,7 +64,8 @@ __global__ void __launch_bounds__(256, LF_SWEEP27_WAVES(T)) k_sweep_lds27(
     const int tz = b / nty;
     const int z0 = tz * zchunk;
     sweep_tile27<T, NH, TX, TY, false>(d1, d2, e1, e2, d1n, d2n, e1n, e2n, N, ZPlanes<T>{}, tx * TX, ty * TY,
-                                       z0, min(z0 + zchunk, N), CoefsOfStep(src, !src.extra && tile == 0), part + (size_t)tile * kNPart);
+                                       z0, min(z0 + zchunk, N), StepCoefs<T, TX, TY>(src, !src.extra && tile == 0),
+                                       part + (size_t)tile * kNPart);
 }
 
 template <typename T, int NH, int TX, int TY>

@@ -28,6 +28,24 @@ struct Coefs {
 #pragma unroll
         for (int j = 0; j < NH; ++j) h[j] = c.h[j];
     }
+    // Every value, and x and y, into scalar registers.  Arithmetic on
+    // floating-point values is vector arithmetic, also of uniform ones, and the
+    // compiler drops a lane read of what it knows to be uniform, or moves it to
+    // where the value came from, and keeps the result in a vector register.  Past
+    // the empty asm it does not know where they came from.
+    __device__ inline void to_scalar(double &x, double &y)
+    {
+        asm("" : "+v"(Cl), "+v"(Cf), "+v"(dt), "+v"(C2), "+v"(g1), "+v"(g2), "+v"(two_g1), "+v"(two_g2),
+                 "+v"(g1sq), "+v"(x), "+v"(y));
+#pragma unroll
+        for (int j = 0; j < NH; ++j) asm("" : "+v"(h[j]));
+        Cl = uniform(Cl); Cf = uniform(Cf); dt = uniform(dt); C2 = uniform(C2); g1 = uniform(g1); g2 = uniform(g2);
+        two_g1 = uniform(two_g1); two_g2 = uniform(two_g2); g1sq = uniform(g1sq);
+#pragma unroll
+        for (int j = 0; j < NH; ++j) h[j] = uniform(h[j]);
+        x = uniform(x);
+        y = uniform(y);
+    }
     // Velocity increments of both fields at one site from the raw stencil
     // sums (s6a, s6b: the integer-weighted neighbour sum including the centre
     // term; Cl carries 1/dx^2 and the stencil weight) and the deviations
@@ -159,11 +177,14 @@ __device__ inline void step_extra_block(const StepSource &q)
 // takes about 2.  Step times, two kernels against one, with wave sums by LDS
 // permutes on both sides: 32^3 FP64 10.8 -> 8.8 us, 128^3 FP32 25.6 -> 23.8,
 // 256^3 114.3 -> 110.9, 512^3 792 -> 789 (7 points).  The coefficients stay in
-// scalar registers: in vector ones (as they were without the measures taken in
-// get() and uniform()) the sweeps that fill the register file spilled inside their
+// scalar registers: in vector ones (as they were without to_scalar() and the scalar
+// loads of get()) the sweeps that fill the register file spilled inside their
 // loops.  FP64 32x16 tiles at 200^3 315 -> 135 us, FP32 64x16 at 256^3 177 -> 126,
 // FP64 27 points at 256^3 246 -> 235, FP32 27 points at 160^3 46.2 -> 43.3.
-// `first`: this block writes the results.
+// SCALAR: FP32 tiles of one site a thread have registers to spare and keep the
+// coefficients in vector ones (27 points, 48^3 10.35 us against 10.7, 100^3 21.35
+// against 21.65).  `first`: this block writes the results.
+template <bool SCALAR>
 struct CoefsOfStep {
     const StepSource &q;
     const bool first;
@@ -187,13 +208,13 @@ struct CoefsOfStep {
         ScaleStep o;
         scale_step(tot, in, NH + 1, o);
         const double g1 = in.g1, g2 = in.g2;
-        c.Cl = uniform((T)o.Cl); c.Cf = uniform((T)o.Cf); c.dt = uniform((T)in.dt); c.C2 = uniform((T)o.C2);
-        c.g1 = uniform((T)g1); c.g2 = uniform((T)g2);
-        c.two_g1 = uniform((T)(2.0 * g1)); c.two_g2 = uniform((T)(2.0 * g2)); c.g1sq = uniform((T)(g1 * g1));
+        c.Cl = (T)o.Cl; c.Cf = (T)o.Cf; c.dt = (T)in.dt; c.C2 = (T)o.C2; c.g1 = (T)g1; c.g2 = (T)g2;
+        c.two_g1 = (T)(2.0 * g1); c.two_g2 = (T)(2.0 * g2); c.g1sq = (T)(g1 * g1);
 #pragma unroll
-        for (int j = 0; j < NH; ++j) c.h[j] = uniform((T)scale_h(o.ch, NH + 1, j + 1, g1));
-        g1n = uniform(o.g1n);
-        g2n = uniform(o.g2n);
+        for (int j = 0; j < NH; ++j) c.h[j] = (T)scale_h(o.ch, NH + 1, j + 1, g1);
+        g1n = o.g1n;
+        g2n = o.g2n;
+        if constexpr (SCALAR) c.to_scalar(g1n, g2n);
         if (first && threadIdx.x == 0) {
             StepResult &r = result();
 #pragma unroll
@@ -220,6 +241,9 @@ private:
         return r;
     }
 };
+
+template <typename T, int TX, int TY>
+using StepCoefs = CoefsOfStep<(TX * TY > 256 || sizeof(T) == 8)>;
 
 // Where the z-planes of the four input arrays (d1, d2, e1, e2) of a z-slab
 // sweep lie.  A sweep reads d on planes [z0-2, z1] and e on [z0-1, z1-1] of
