@@ -99,7 +99,10 @@ int resident_blocks(const lf_params *p, int tile_x, int tile_y)
 // before it (tiles by N alone, chunks of 8 to 64 planes filling all resident
 // blocks) was 17% (FP32, 27 points) to 30% (FP64, 7 points) off: 32^3 FP64
 // 16.6 -> 7.9 us a step, 128^3 FP32 26.8 -> 22.9, 200^3 FP32 88.1 -> 66.3,
-// 320^3 FP64 666 -> 430; 256^3 and 512^3 FP32 keep their shapes.
+// 320^3 FP64 666 -> 430; 256^3 and 512^3 FP32 keep their shapes.  FP64 with 27
+// points: 64x4 costs 0.64 of 64x8 since the latter no longer spills (0.53 before),
+// and 64x8 runs at 128^3 (43.0 -> 41.2 us) and at 160^3 (79.5 -> 74.0, 77.9 by the
+// rule before).
 struct TileCost {
     int tx, ty;
     double plane;
@@ -118,7 +121,7 @@ const ShapeModel &shape_model(int dtype, int stencil)
         {{128, 8, 1.57}, {64, 16, 1.65}, {64, 8, 1.0}, {64, 4, 0.65}, {0, 0, 0}}, 3, 0.79, 1.09};
     static const ShapeModel f64_7 = {
         {{128, 4, 0.92}, {64, 8, 1.0}, {64, 4, 1.02}, {32, 8, 0.68}, {0, 0, 0}}, 1, 0.64, 1.18};
-    static const ShapeModel f64_27 = {{{64, 8, 1.0}, {64, 4, 0.53}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, 6, 0.65, 1.0};
+    static const ShapeModel f64_27 = {{{64, 8, 1.0}, {64, 4, 0.64}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, 6, 0.65, 1.0};
     return dtype == LF_F64 ? (stencil == 27 ? f64_27 : f64_7) : (stencil == 27 ? f32_27 : f32_7);
 }
 
