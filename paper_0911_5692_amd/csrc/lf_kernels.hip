@@ -522,36 +522,41 @@ __global__ void __launch_bounds__(kStage2Threads) k_rho_p_final(const double *pa
 // A block takes kFlat x 256 sites in address order, all of its loads in flight
 // at once, and streams the results (non-temporal): FP32 to FP32 at 512^3 785
 // us a call against 925 for a grid-stride loop of plain stores (835 with one
-// site a thread, 855 with four), at 256^3 104 against 154.
+// site a thread, 855 with four), at 256^3 104 against 154.  WANT: the outputs
+// that are written, bit j for f1, f2, v1, v2; a kernel each, so that arrays no
+// output needs are not read and the loads stay unconditional (with conditional
+// ones all four outputs took 926 us instead of 723).
 constexpr int kFlat = 2;
 
-template <typename T, typename To>
+template <typename T, typename To, int WANT>
 __global__ void __launch_bounds__(256) k_get_fields(const T *__restrict__ d1, const T *__restrict__ d2,
                                                     const T *__restrict__ e1, const T *__restrict__ e2,
-                                                    To *f1, To *f2, To *v1, To *v2, int N,
-                                                    const DevParams *__restrict__ P,
+                                                    To *f1, To *f2, To *v1, To *v2, const int64_t start,
+                                                    const int64_t N3, const DevParams *__restrict__ P,
                                                     const DevScalars *__restrict__ S, int sync)
 {
-    const int64_t N3 = (int64_t)N * N * N;
+    constexpr bool F1 = WANT & 1, F2 = WANT & 2, V1 = WANT & 4, V2 = WANT & 8;
     const double h = sync ? 0.5 * P->dt : 0.0;
     const double g1 = S->bg_f[0] - h * S->bg_v[0], g2 = S->bg_f[1] - h * S->bg_v[1];
     const double vb1 = S->bg_v[0], vb2 = S->bg_v[1];
-    const int64_t i0 = (int64_t)blockIdx.x * (256 * kFlat) + threadIdx.x;
+    const int64_t i0 = start + (int64_t)blockIdx.x * (256 * kFlat) + threadIdx.x;
     T v[kFlat][4];
 #pragma unroll
     for (int k = 0; k < kFlat; ++k) {
         const int64_t i = i0 + 256 * k < N3 ? i0 + 256 * k : N3 - 1;
-        v[k][0] = d1[i]; v[k][1] = d2[i]; v[k][2] = e1[i]; v[k][3] = e2[i];
+        if constexpr (F1) v[k][0] = d1[i];
+        if constexpr (F2) v[k][1] = d2[i];
+        if constexpr (F1 || V1) v[k][2] = e1[i];
+        if constexpr (F2 || V2) v[k][3] = e2[i];
     }
 #pragma unroll
     for (int k = 0; k < kFlat; ++k) {
         const int64_t i = i0 + 256 * k;
         if (i >= N3) break;
-        const double p = (double)v[k][2], q = (double)v[k][3];
-        if (f1) __builtin_nontemporal_store((To)(g1 + ((double)v[k][0] - h * p)), f1 + i);
-        if (f2) __builtin_nontemporal_store((To)(g2 + ((double)v[k][1] - h * q)), f2 + i);
-        if (v1) __builtin_nontemporal_store((To)(vb1 + p), v1 + i);
-        if (v2) __builtin_nontemporal_store((To)(vb2 + q), v2 + i);
+        if constexpr (F1) __builtin_nontemporal_store((To)(g1 + ((double)v[k][0] - h * (double)v[k][2])), f1 + i);
+        if constexpr (F2) __builtin_nontemporal_store((To)(g2 + ((double)v[k][1] - h * (double)v[k][3])), f2 + i);
+        if constexpr (V1) __builtin_nontemporal_store((To)(vb1 + (double)v[k][2]), v1 + i);
+        if constexpr (V2) __builtin_nontemporal_store((To)(vb2 + (double)v[k][3]), v2 + i);
     }
 }
 
@@ -772,14 +777,29 @@ void launch_energy_ens(int stencil, int dtype, const EnsEntry *tab, int R, int g
     hipLaunchKernelGGL(k_energy_final_ens, dim3(R), dim3(kStage2Threads), 0, st, tab, parity, out_dev);
 }
 
-template <typename T, typename To>
+// A launch holds less than 2^32 threads, which one of all sites would exceed at
+// 2048^3: above 512^3 the sites are dealt to several.
+constexpr int64_t kFlatLaunch = (int64_t)1 << 27;
+
+template <typename T, typename To, int WANT = 15>
 static void get_fields_t(const void *const s4[4], void *const o[4], int N, const DevParams *P,
                          const DevScalars *S, int sync, hipStream_t st)
 {
-    const int64_t N3 = (int64_t)N * N * N;
-    hipLaunchKernelGGL((k_get_fields<T, To>), dim3((unsigned)((N3 + 256 * kFlat - 1) / (256 * kFlat))), dim3(256), 0, st,
-                       (const T *)s4[0], (const T *)s4[1], (const T *)s4[2], (const T *)s4[3],
-                       (To *)o[0], (To *)o[1], (To *)o[2], (To *)o[3], N, P, S, sync);
+    if constexpr (WANT > 0) {
+        const int want = (o[0] ? 1 : 0) | (o[1] ? 2 : 0) | (o[2] ? 4 : 0) | (o[3] ? 8 : 0);
+        if (want != WANT) {
+            get_fields_t<T, To, WANT - 1>(s4, o, N, P, S, sync, st);
+            return;
+        }
+        const int64_t N3 = (int64_t)N * N * N;
+        for (int64_t start = 0; start < N3; start += kFlatLaunch) {
+            const int64_t n = N3 - start < kFlatLaunch ? N3 - start : kFlatLaunch;
+            hipLaunchKernelGGL((k_get_fields<T, To, WANT>), dim3((unsigned)((n + 256 * kFlat - 1) / (256 * kFlat))),
+                               dim3(256), 0, st, (const T *)s4[0], (const T *)s4[1], (const T *)s4[2],
+                               (const T *)s4[3], (To *)o[0], (To *)o[1], (To *)o[2], (To *)o[3], start, N3, P, S,
+                               sync);
+        }
+    }
 }
 
 void launch_get_fields(int dtype, int out_dtype, const void *const s4[4], void *const out[4], int N,
