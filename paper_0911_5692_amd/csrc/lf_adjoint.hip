@@ -458,15 +458,15 @@ __global__ void __launch_bounds__(256) k_adj_desync(int64_t N3, double h, const 
                                                     double *__restrict__ gf2, double *__restrict__ gv1,
                                                     double *__restrict__ gv2, double *A)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < N3) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N3;
+         i += (int64_t)gridDim.x * blockDim.x) {
         const double a = lf1[i], b = lf2[i];
         gf1[i] = a;
         gf2[i] = b;
         gv1[i] = mu1[i] - h * a;
         gv2[i] = mu2[i] - h * b;
     }
-    if (i == 0) A[1] += h * A[0];
+    if (blockIdx.x == 0 && threadIdx.x == 0) A[1] += h * A[0];
 }
 
 // ------------------------------------------------------------ launchers
@@ -567,8 +567,9 @@ void launch_adj_step(int stencil, int dtype, const AdjStep &a, int N, int beta, 
 void launch_adj_desync(int N, double dt, double *const lam[4], double *const grad[4], double *A, hipStream_t st)
 {
     const int64_t N3 = (int64_t)N * N * N;
-    hipLaunchKernelGGL(k_adj_desync, dim3((unsigned)((N3 + 255) / 256)), dim3(256), 0, st, N3, 0.5 * dt, lam[0], lam[1],
-                       lam[2], lam[3], grad[0], grad[1], grad[2], grad[3], A);
+    const int64_t g = (N3 + 255) / 256;  // at most 65536 blocks: a launch holds less than 2^32 threads
+    hipLaunchKernelGGL(k_adj_desync, dim3((unsigned)(g > 65536 ? 65536 : g)), dim3(256), 0, st, N3, 0.5 * dt, lam[0],
+                       lam[1], lam[2], lam[3], grad[0], grad[1], grad[2], grad[3], A);
 }
 
 }  // namespace lf
