@@ -1521,7 +1521,7 @@ int lf_autotune(const lf_params *p, void *stream, void *workspace, size_t ws_byt
         c->inited = 1;
         c->cur = 0;
         double ms = 0.0;
-        rc = lf_step(c, 3);
+        rc = lf_step(c, 4);  // even: the timed call starts from the parity of the long graphs
         if (!rc) rc = lf_step(c, steps);
         if (!rc) rc = lf_last_step_ms(c, &ms);
         lf_destroy(c);

@@ -499,8 +499,8 @@ int fft_stride(int N, int nk)
     return (nk + b - 1) / b * b;
 }
 
-// Sources of the x pass: operator()(i) is the value at site i; kLoads: it is
-// read from memory, and four(i, v) reads four.
+// Sources of the x pass.  kLoads: read from memory, four(i, v) gives the values of
+// four sites from i; otherwise computed, operator()(i) gives that of site i.
 template <typename T>
 struct SyncSource {  // synchronised deviation of a field, or a velocity's deviation
     static constexpr bool kLoads = true;
@@ -508,7 +508,6 @@ struct SyncSource {  // synchronised deviation of a field, or a velocity's devia
     double h;
     int velocity;
     __device__ inline double value(T dv, T ev) const { return velocity ? (double)ev : (double)dv - h * (double)ev; }
-    __device__ inline double operator()(long long i) const { return value(velocity ? T(0) : d[i], e[i]); }
     // four consecutive elements from i, a multiple of four (the arrays start
     // on 256 bytes)
     __device__ inline void four(long long i, double (&v)[4]) const

@@ -763,16 +763,13 @@ void ens_diag_shape(int stencil, int rows, EnsEntry *e)
 void launch_energy_ens(int stencil, int dtype, const EnsEntry *tab, int R, int gmax, int parity, double *out_dev,
                        hipStream_t st)
 {
-    const dim3 block(256);
-    for (int r = 0; r < R; r += 65535) {  // the most block rows of a launch
-        const dim3 grid(gmax, R - r < 65535 ? R - r : 65535);
-        if (stencil == 27) {
-            if (dtype == 0) hipLaunchKernelGGL((k_diag_ens<float, 27>), grid, block, 0, st, tab + r, parity);
-            else hipLaunchKernelGGL((k_diag_ens<double, 27>), grid, block, 0, st, tab + r, parity);
-        } else {
-            if (dtype == 0) hipLaunchKernelGGL((k_diag_ens<float, 7>), grid, block, 0, st, tab + r, parity);
-            else hipLaunchKernelGGL((k_diag_ens<double, 7>), grid, block, 0, st, tab + r, parity);
-        }
+    const dim3 grid(gmax, R), block(256);
+    if (stencil == 27) {
+        if (dtype == 0) hipLaunchKernelGGL((k_diag_ens<float, 27>), grid, block, 0, st, tab, parity);
+        else hipLaunchKernelGGL((k_diag_ens<double, 27>), grid, block, 0, st, tab, parity);
+    } else {
+        if (dtype == 0) hipLaunchKernelGGL((k_diag_ens<float, 7>), grid, block, 0, st, tab, parity);
+        else hipLaunchKernelGGL((k_diag_ens<double, 7>), grid, block, 0, st, tab, parity);
     }
     hipLaunchKernelGGL(k_energy_final_ens, dim3(R), dim3(kStage2Threads), 0, st, tab, parity, out_dev);
 }
