@@ -71,9 +71,11 @@ def white_noise(N: int, seed: int, j: int, sites=None) -> np.ndarray:
 
 
 def mode_norm(N: int) -> np.ndarray:
-    """|n| of every rfftn mode, n the FFT-signed integer wavevector."""
-    n0 = np.fft.fftfreq(N) * N
-    n2 = np.fft.rfftfreq(N) * N
+    """|n| of every rfftn mode, n the FFT-signed integer wavevector.  Whole
+    numbers: fftfreq(N) * N misses some by a rounding (9, 13 and 18 at N = 125),
+    which would decide whether a mode at the cutoff is kept."""
+    n0 = np.rint(np.fft.fftfreq(N) * N)
+    n2 = np.rint(np.fft.rfftfreq(N) * N)
     return np.sqrt(n0[:, None, None] ** 2 + n0[None, :, None] ** 2 + n2[None, None, :] ** 2)
 
 
