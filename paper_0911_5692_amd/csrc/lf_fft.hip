@@ -468,7 +468,8 @@ __global__ void __launch_bounds__(1024) k_spectrum_final(const double *__restric
 
 // Waves per SIMD the passes are compiled for: two blocks of 512 threads per CU
 // with the butterflies of 2, 4 and 8 points; those of 3, 5 and 7 need more
-// registers.
+// registers.  In blocks of 1024 threads, where four waves are all there can be,
+// they spill 57 to 70 of them.
 constexpr int fft_waves(int nt, bool exact) { return exact || nt == 1024 ? 4 : 2; }
 
 // Lines per block and threads of the passes over N-point lines: B 16-byte
@@ -850,14 +851,19 @@ int spectrum_bins(int N)
 
 namespace {
 
-// Sizes that go through the line passes; the others, and those where they are
-// no faster, through hipFFT.  Both ways measured (spectra of four fields; the
-// whole vacuum state; us):
-//   powers of two from 128: 128^3 667 -> 518 and 497 -> 339, 256^3 1775 -> 1168
-//     and 2505 -> 1223, 512^3 11090 -> 6400 and 22210 -> 7070;
-//   factors of 3, 5 and 7, whose butterflies leave one block per CU: vacuum
-//     100^3 388 -> 316, 210^3 1831 -> 1472, 400^3 13382 -> 7706; but spectra
-//     200^3 980 -> 1138, 400^3 6965 -> 7269;
+// Sizes that go through the line passes; the others through hipFFT.  Both ways
+// measured (spectra of four fields; the whole vacuum state; us; library -> own):
+//   powers of two from 128: 128^3 667 -> 518 and 497 -> 301, 256^3 1775 -> 1140
+//     and 2590 -> 1010, 512^3 11090 -> 6400 and 22150 -> 7070, 1024^3 108 -> 58 ms
+//     and 222 -> 71 ms;
+//   factors of 3, 5 and 7: vacuum at the default cutoff 100^3 393 -> 300, 144^3
+//     640 -> 628, 210^3 1876 -> 1344, 270^3 3109 -> 3268 (the one that is slower of 47
+//     from 96 to 1000), 400^3 13360 -> 6980, 600^3 46.4 -> 34.4 ms, 768^3 97 -> 50,
+//     1000^3 218 -> 117.  With all modes kept even sizes with few factors are up to
+//     1.7 times slower (200^3 1307 -> 1571, 270^3 3126 -> 5197, 540^3 29.2 -> 47.7 ms,
+//     600^3 46.4 -> 62.0), but the library first plans for 1.6 to 2.0 s per size and
+//     process, which is hundreds to thousands of such calls.  Spectra were not
+//     faster: 200^3 980 -> 1138, 400^3 6965 -> 7269;
 //   small: 64^3 370 -> 410 and 176 -> 196 (few blocks, as many launches).
 bool spectrum_own(int N) { return N >= 128 && (N & (N - 1)) == 0; }
 bool vacuum_own(int N) { return N >= 96 && fft_plan(N).stages > 0; }
