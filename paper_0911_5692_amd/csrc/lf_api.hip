@@ -73,9 +73,9 @@ int cu_count()
     return cus > 0 ? cus : 256;
 }
 
-int resident_blocks(const lf_params *p, int tile_x, int tile_y)
+int resident_blocks(const lf_params *p, int tile_x, int tile_y, bool ens)
 {
-    int per_cu = sweep_lds_blocks_per_cu(stencil_of(p), p->dtype, tile_x, tile_y, p->beta);
+    int per_cu = sweep_blocks_per_cu(stencil_of(p), p->dtype, tile_x, tile_y, p->beta, ens);
     (void)hipGetLastError();
     if (per_cu <= 0) per_cu = 3;
     return per_cu * cu_count();
@@ -553,7 +553,7 @@ int lf_create(const lf_params *p, void *stream, void *workspace, size_t ws_bytes
     // block has to write (32^3 FP64: 8.0 us a step against 8.8 with that work
     // at the end of a tile's block); in a full one it would wait for a tile's
     // block to end
-    c->extra = c->sh.tile_y != 1 && c->sh.rows < resident_blocks(p, c->sh.tile_x, c->sh.tile_y) ? 1 : 0;
+    c->extra = c->sh.tile_y != 1 && c->sh.rows < resident_blocks(p, c->sh.tile_x, c->sh.tile_y, false) ? 1 : 0;
     hipError_t e;
     DevParams dp;
     fill_dev_params(p, &dp);
@@ -1850,7 +1850,7 @@ int lf_ens_create(int R, const lf_params *per, void *stream, void *workspace, si
     }
     // persistent grid: as many blocks as fit on the device at once
     const lf_params q0 = ens_sub_params(&per[0], &per[0], 8);
-    int res = resident_blocks(&q0, e->tile_x, e->tile_y);
+    int res = resident_blocks(&q0, e->tile_x, e->tile_y, true);
     e->grid = nitems < res ? nitems : res;
     if ((rc = ens_prepare_graphs(e))) {
         lf_ens_destroy(e);

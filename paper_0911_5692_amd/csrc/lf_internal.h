@@ -166,16 +166,16 @@ int sweep_lds_blocks(int N, int tile_x, int tile_y, int zchunk);
 // blocks (= partial rows) of a sweep over nz planes of an N x N x nz block
 int sweep_io_blocks(int N, int nz, int tile_x, int tile_y, int zchunk);
 // 27-point LDS sweep (lf_sweep27.hip); launch_sweep_lds / launch_sweep_ens /
-// sweep_lds_blocks_per_cu dispatch to these for stencil 27.
+// sweep_blocks_per_cu dispatch to these for stencil 27.
 void launch_sweep_lds27(int dtype, int tile_x, int tile_y, int beta, const void *const in[4],
                         void *const out[4], int N, int zchunk, const StepSource &src, double *part,
                         hipStream_t st);
 void launch_sweep_ens27(int dtype, int tile_x, int tile_y, int beta, const EnsEntry *tab,
                         const int4 *items, int nitems, int *queue, int grid, int parity, hipStream_t st);
-int sweep_lds27_blocks_per_cu(int dtype, int tile_x, int tile_y, int beta);
-// Resident blocks per CU of the LDS sweep instantiation (0 if unknown, e.g.
-// no device).
-int sweep_lds_blocks_per_cu(int stencil, int dtype, int tile_x, int tile_y, int beta);
+int sweep27_blocks_per_cu(int dtype, int tile_x, int tile_y, int beta, bool ens);
+// Resident blocks per CU of the LDS sweep instantiation, a lone lattice's or an
+// ensemble's (0 if unknown, e.g. no device).
+int sweep_blocks_per_cu(int stencil, int dtype, int tile_x, int tile_y, int beta, bool ens);
 void launch_energy(int stencil, int dtype, const void *const st4[4], int N, const DevParams *P,
                    const DevScalars *S, double *part, int nblk, double *out_dev, hipStream_t st);
 // Energies of R realizations, kEnOut numbers each at out_dev; gmax: the largest

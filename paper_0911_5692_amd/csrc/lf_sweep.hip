@@ -243,38 +243,45 @@ static void sweep_lds_y(int tile_x, int tile_y, int beta, const void *const in[4
     }
 }
 
-template <typename T, int TX, int TY>
-static int occ_b(int beta)
+template <typename T, int NH, int TX, int TY>
+static int occ_t(bool ens)
 {
     int nb = 0;
-    hipError_t e;
-    constexpr size_t lds = two_per_cu<T, TX, TY>();
-    switch (beta) {
-    case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep_lds<T, 1, TX, TY>, 256, lds); break;
-    case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep_lds<T, 2, TX, TY>, 256, lds); break;
-    case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep_lds<T, 3, TX, TY>, 256, lds); break;
-    case 5: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep_lds<T, 4, TX, TY>, 256, lds); break;
-    default: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep_lds<T, 5, TX, TY>, 256, lds); break;
-    }
+    const hipError_t e =
+        ens ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep_ens<T, NH, TX, TY>, 256, 0)
+            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep_lds<T, NH, TX, TY>, 256,
+                                                           (two_per_cu<T, TX, TY>()));
     return e == hipSuccess ? nb : 0;
 }
 
-template <typename T>
-static int occ_y(int tile_x, int tile_y, int beta)
+template <typename T, int TX, int TY>
+static int occ_b(int beta, bool ens)
 {
-    if (tile_x == 128) return tile_y == 4 ? occ_b<T, 128, 4>(beta) : occ_b<T, 128, 8>(beta);
-    if (tile_x == 32) return tile_y == 8 ? occ_b<T, 32, 8>(beta) : occ_b<T, 32, 16>(beta);
-    switch (tile_y) {
-    case 4: return occ_b<T, 64, 4>(beta);
-    case 8: return occ_b<T, 64, 8>(beta);
-    default: return occ_b<T, 64, 16>(beta);
+    switch (beta) {
+    case 2: return occ_t<T, 1, TX, TY>(ens);
+    case 3: return occ_t<T, 2, TX, TY>(ens);
+    case 4: return occ_t<T, 3, TX, TY>(ens);
+    case 5: return occ_t<T, 4, TX, TY>(ens);
+    default: return occ_t<T, 5, TX, TY>(ens);
     }
 }
 
-int sweep_lds_blocks_per_cu(int stencil, int dtype, int tile_x, int tile_y, int beta)
+template <typename T>
+static int occ_y(int tile_x, int tile_y, int beta, bool ens)
 {
-    if (stencil == 27) return sweep_lds27_blocks_per_cu(dtype, tile_x, tile_y, beta);
-    return dtype == 0 ? occ_y<float>(tile_x, tile_y, beta) : occ_y<double>(tile_x, tile_y, beta);
+    if (tile_x == 128) return tile_y == 4 ? occ_b<T, 128, 4>(beta, ens) : occ_b<T, 128, 8>(beta, ens);
+    if (tile_x == 32) return tile_y == 8 ? occ_b<T, 32, 8>(beta, ens) : occ_b<T, 32, 16>(beta, ens);
+    switch (tile_y) {
+    case 4: return occ_b<T, 64, 4>(beta, ens);
+    case 8: return occ_b<T, 64, 8>(beta, ens);
+    default: return occ_b<T, 64, 16>(beta, ens);
+    }
+}
+
+int sweep_blocks_per_cu(int stencil, int dtype, int tile_x, int tile_y, int beta, bool ens)
+{
+    if (stencil == 27) return sweep27_blocks_per_cu(dtype, tile_x, tile_y, beta, ens);
+    return dtype == 0 ? occ_y<float>(tile_x, tile_y, beta, ens) : occ_y<double>(tile_x, tile_y, beta, ens);
 }
 
 template <typename T, int NH, int TX, int TY>

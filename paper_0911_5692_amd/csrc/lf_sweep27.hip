@@ -122,7 +122,7 @@ void ens27_t(int tile_x, int tile_y, int beta, const EnsEntry *tab, const int4 *
 }
 
 template <typename T>
-int occ27_t(int tile_x, int tile_y, int beta)
+int occ27_t(int tile_x, int tile_y, int beta, bool ens)
 {
     int nb = 0;
     hipError_t e = hipErrorInvalidValue;
@@ -130,7 +130,8 @@ int occ27_t(int tile_x, int tile_y, int beta)
         constexpr int TX = decltype(tx)::value, TY = decltype(ty)::value;
         with_nh(beta, [&](auto nh) {
             constexpr int NH = decltype(nh)::value;
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep_lds27<T, NH, TX, TY>, 256, 0);
+            e = ens ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep_ens27<T, NH, TX, TY>, 256, 0)
+                    : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep_lds27<T, NH, TX, TY>, 256, 0);
         });
     });
     return e == hipSuccess ? nb : 0;
@@ -153,9 +154,9 @@ void launch_sweep_ens27(int dtype, int tile_x, int tile_y, int beta, const EnsEn
     else ens27_t<double>(tile_x, tile_y, beta, tab, items, nitems, queue, grid, parity, st);
 }
 
-int sweep_lds27_blocks_per_cu(int dtype, int tile_x, int tile_y, int beta)
+int sweep27_blocks_per_cu(int dtype, int tile_x, int tile_y, int beta, bool ens)
 {
-    return dtype == 0 ? occ27_t<float>(tile_x, tile_y, beta) : occ27_t<double>(tile_x, tile_y, beta);
+    return dtype == 0 ? occ27_t<float>(tile_x, tile_y, beta, ens) : occ27_t<double>(tile_x, tile_y, beta, ens);
 }
 
 }  // namespace lf
