@@ -395,9 +395,10 @@ int lf_ens_zchunk(int N, int target);
 /* Measurement: run n >= 1 steps outside any graph with HIP events around
  * each kernel of the step (on the context's stream) and return the average
  * duration in ms of kernel j in ms[j], j < n_out:
- *   0 = scale-factor update (0 when the sweep forms it in its own blocks:
- *   LDS sweeps of at most 1024 blocks), 1 = kick-drift sweep, 2 = separate
- *   reduction (0 when the sweep computes it in-sweep).  Blocking.  Advances the state. */
+ *   0 = scale-factor update, 1 = kick-drift sweep, 2 = separate reduction.
+ * Where the sweep does the work of 0 (LDS sweeps of at most 1024 blocks) or of
+ * 2 (every LDS sweep) in its own blocks, that entry is the time between two
+ * events with no kernel between them.  Blocking.  Advances the state. */
 int lf_time_kernels(lf_ctx *ctx, int64_t n, double *ms, int n_out);
 
 /* ---- vacuum initial state on the device (Sec. II.B) --------------------
